@@ -30,7 +30,8 @@
  *       y[n,k,i,j] = sum_c sum_{r,s<3} x[n,c,i+r-pad,j+s-pad] * g[k,c,r,s]
  *     with x read as zero outside [0,H) x [0,W).
  *   - Floating point is IEEE fp32 storage and fp32 arithmetic (the paper's
- *     precision, Sec. 3); FMA contraction is allowed; the GEMMs run on fp32 MFMA.
+ *     precision, Sec. 3); FMA contraction is allowed; the GEMMs run on fp32 MFMA,
+ *     or on exact three-term splits of their fp32 operands (WINO_ALGO_AUTO below).
  *   - Size limits of the NCHW (channel-first) paths, from the kernels' 32-bit
  *     offsets into x: one image's input, C*H*W*4 bytes, must be below 1 GiB for
  *     the fused and split algorithms, and (16 / (th*tw) + 2) such images below
@@ -130,6 +131,17 @@ extern "C" {
  * WINO_CSLICES(1) keeps AUTO from slicing. */
 #define WINO_CSLICES(n)    (((unsigned)(n) & 0xFu) << 20)
 
+/* WINO_ALGO_AUTO runs large fp32 "same" layers (pad (r-1)/2, NCHW) on the bf16
+ * matrix cores: U and V are split exactly into three bf16 terms each (24
+ * significand bits, the whole fp32 exponent range) and the six largest of the
+ * nine products are summed in fp32, for 2.67 times the fp32 matrix rate.  The
+ * dropped products are below 2^-21 of |u v|; errors against 64 bits are no
+ * larger than the fp32 kernels'.  An infinite or NaN input gives NaN wherever
+ * those give an infinity or NaN.  The filters' split goes to the workspace
+ * (6 bytes per element of U, with the channels in whole steps of 16) in every
+ * call; without that workspace AUTO runs the kernels below.  An explicitly
+ * chosen algorithm always runs on fp32 MFMA. */
+
 /* Human-readable text of a status code (static storage, never NULL). */
 const char* wino_status_string(int status);
 
@@ -164,7 +176,8 @@ int wino_filter_transform(const float* g, float* U, int C, int K, int m, void* s
 
 /* The planner's choice for a layer (r = 3, or 5 with m = 2), for callers that
  * pass the workspace wino_workspace_bytes(_r) reports: *algo = the
- * WINO_ALGO_* value that runs (FUSED, SPLIT, STAGED or LOWC), *slices = the
+ * WINO_ALGO_* value that runs (FUSED, SPLIT, STAGED or LOWC; where AUTO uses the
+ * bf16 matrix cores, the one that they stand in for), *slices = the
  * fused kernel's channel slices (1 when unsliced or not fused).  Errors as for
  * wino_workspace_bytes_r's arguments (INVALID_ARG, UNSUPPORTED); null outputs
  * are INVALID_ARG. */

@@ -13,8 +13,9 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libwino.so")
-SOURCES = [os.path.join(CSRC, "wino_kernels.hip"), os.path.join(CSRC, "wino_api.cpp")]
-HEADERS = [os.path.join(CSRC, f) for f in ("wino_transforms.h", "wino_internal.h")] + [
+KERNELS = [os.path.join(CSRC, f) for f in ("wino_kernels.hip", "wino_bf3.hip")]
+SOURCES = KERNELS + [os.path.join(CSRC, "wino_api.cpp")]
+HEADERS = [os.path.join(CSRC, f) for f in ("wino_device.h", "wino_transforms.h", "wino_internal.h")] + [
     os.path.join(ROOT, "include", "wino.h")]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -37,16 +38,15 @@ def build(verbose: bool = False) -> str:
 
 def device_asm() -> str:
     """gfx950 assembly of the kernels (for inspection and the packed-op check)."""
-    cmd = [HIPCC] + COMMON + DEVICE_FLAGS + ["--cuda-device-only", "-S", "-o", "-", SOURCES[0]]
-    return subprocess.check_output(cmd, text=True)
+    cmd = [HIPCC] + COMMON + DEVICE_FLAGS + ["--cuda-device-only", "-S", "-o", "-"]
+    return "".join(subprocess.check_output(cmd + [k], text=True) for k in KERNELS)
 
 
 def resource_usage() -> str:
     """Per-kernel VGPR/AGPR/spill/occupancy report from the compiler."""
     cmd = [HIPCC] + COMMON + DEVICE_FLAGS + ["--cuda-device-only", "-c", "-o", os.devnull,
-                                             "-Rpass-analysis=kernel-resource-usage", SOURCES[0]]
-    p = subprocess.run(cmd, capture_output=True, text=True, check=True)
-    return p.stderr
+                                             "-Rpass-analysis=kernel-resource-usage"]
+    return "".join(subprocess.run(cmd + [k], capture_output=True, text=True, check=True).stderr for k in KERNELS)
 
 
 def check_no_packed_fp32(asm: str | None = None) -> None:

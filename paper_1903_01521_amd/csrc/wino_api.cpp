@@ -101,6 +101,8 @@ struct Plan {
     unsigned algo;        // WINO_ALGO_FUSED, WINO_ALGO_SPLIT or WINO_ALGO_STAGED
     bool automatic;       // chosen by the planner (split falls back to fused without workspace)
     FusedCfg cfg;
+    bool bf3;             // on the bf16 matrix cores, the operands split exactly in three (launch_bf3)
+    size_t need;          // workspace of SPLIT, of FUSED with slices, and of bf3
 };
 
 // Row groups per unit of the fused kernel: alpha = 4 (F(2x2,3x3)) keeps all
@@ -167,6 +169,14 @@ size_t slice_workspace(const Geom& g, int nsl) {
     return (size_t)slices_used(g, nsl) * g.N * g.K * g.Ho * g.Wo * sizeof(float);
 }
 
+// AUTO runs a layer that it gives the fused or split kernel on the bf16 matrix
+// cores instead where their estimate is 5% shorter (the estimates are that
+// good); with less workspace than that needs, the kernel it was given to runs.
+constexpr double kBf3Margin = 0.95;
+// fused_ns leaves out a round's fixed part (2.5 us: what the measured times of
+// 27 layers from 10 to 72 us lie above it at least).
+double fused_full_ns(const Geom& g, FusedCfg c) { return fused_ns(g, c) + 2500.0 * rounds(fused_workgroups(g, c)); }
+
 // Offsets into x that the NCHW input kernels form (see kInvalidOffset): one
 // image for the fused and split kernels; for the staged input transforms the
 // images one 16-tile block spans, at most 16 / (th*tw) + 2.
@@ -208,6 +218,7 @@ bool prec_offsets_fit(const Geom& g) {
 }
 
 bool plan_fits(const Geom& g, const Plan& p) {
+    if (p.bf3) return true;                            // bf3_takes
     if (p.algo == WINO_ALGO_STAGED) return block_images_fit(g);
     if (p.algo == WINO_ALGO_FUSED) return image_fits(g) && fused_offsets_fit(g, p.cfg);
     if (p.algo == WINO_ALGO_SPLIT) return image_fits(g) && split_offsets_fit(g);
@@ -228,6 +239,7 @@ int make_plan(const Geom& g, unsigned flags, Plan* p) {
     if (p->algo == WINO_ALGO_FUSED && g.r == 3) {
         Plan q = *p;
         q.algo = WINO_ALGO_SPLIT;
+        q.need = split_workspace(g);
         q.cfg.nsl = 1;
         if (plan_fits(g, q)) {
             *p = q;
@@ -266,6 +278,8 @@ int make_plan_unchecked(const Geom& g, unsigned flags, Plan* p) {
             return WINO_ERR_UNSUPPORTED;
         p->automatic = algo == WINO_ALGO_AUTO;
         p->cfg = FusedCfg{1, 16, 1};
+        p->bf3 = false;
+        p->need = 0;
         // AUTO: split on layers with at least two full rounds of its items
         // (tile-block pair x filter group) on the CUs, where the saved M round
         // trip outweighs its per-item prologue and epilogue.
@@ -306,6 +320,8 @@ int make_plan_unchecked(const Geom& g, unsigned flags, Plan* p) {
     // The fused and split kernels address U through a 32-bit buffer range.
     if (p->algo != WINO_ALGO_STAGED && (int64_t)g.KB * g.CQ * g.T * 256 > 0x7fffffffLL) return WINO_ERR_UNSUPPORTED;
     p->cfg = c;
+    p->bf3 = false;
+    p->need = 0;
     // Layers with at most 4 channels: the low-C kernel.
     if (p->automatic && g.r == 3 && g.C <= 4 && !cs_req && !blk) {
         p->algo = WINO_ALGO_LOWC;
@@ -314,6 +330,16 @@ int make_plan_unchecked(const Geom& g, unsigned flags, Plan* p) {
     // Split path where the estimates favour it.
     if (p->automatic && g.r == 3 && !cs_req && split_ns(g) < fused_ns(g, c))
         p->algo = WINO_ALGO_SPLIT;
+    if (p->algo == WINO_ALGO_SPLIT) {
+        p->need = split_workspace(g);
+        p->bf3 = p->automatic && bf3_takes(g) && bf3_workspace(g) <= p->need && bf3_ns(g) < kBf3Margin * split_ns(g);
+        return WINO_OK;
+    }
+    if (p->automatic && !cs_req && !blk && bf3_takes(g) && bf3_ns(g) < kBf3Margin * fused_full_ns(g, c)) {
+        p->bf3 = true;
+        p->need = bf3_workspace(g);
+        return WINO_OK;
+    }
     // Channel slices over workgroups for fused layers that leave CUs idle with
     // a long channel loop each (deep layers at small batch): double the slices
     // while the workgroups still fit one round on the 256 CUs and every slice
@@ -398,9 +424,9 @@ size_t wino_workspace_bytes_r(int N, int C, int H, int W, int K, int pad, int m,
         return (size_t)-1;
     if (prec_of(flags) && p.algo == WINO_ALGO_SPLIT) return split16_workspace(g);
     if (prec_of(flags)) return round_up(vh_bytes(g), 256) + m_elems(g) * sizeof(float);
+    if (p.algo == WINO_ALGO_SPLIT || p.bf3) return p.need;
     if (p.algo == WINO_ALGO_FUSED && p.cfg.nsl > 1) return slice_workspace(g, p.cfg.nsl);
     if (p.algo == WINO_ALGO_FUSED || p.algo == WINO_ALGO_LOWC) return 0;
-    if (p.algo == WINO_ALGO_SPLIT) return split_workspace(g);
     return round_up(v_elems(g) * sizeof(float), 256) + m_elems(g) * sizeof(float);
 }
 
@@ -476,15 +502,17 @@ int wino_conv2d_r(const float* x, const float* U, float* y, int N, int C, int H,
             return WINO_ERR_INVALID_ARG;
         return hip_status(launch_staged16(x, U, y, workspace, (float*)((char*)workspace + vb), g, prec, relu, s));
     }
-    if (p.algo == WINO_ALGO_SPLIT) {
-        const size_t need = split_workspace(g);
+    if (p.algo == WINO_ALGO_SPLIT || p.bf3) {
+        const size_t need = p.need;
         if (!workspace || workspace_bytes < need) {
             if (!p.automatic) return WINO_ERR_WORKSPACE;
-            p.algo = WINO_ALGO_FUSED;          // no room for V: the fused kernel, where its offsets fit
+            p.algo = WINO_ALGO_FUSED;          // no room: the fused kernel, where its offsets fit
+            p.bf3 = false;
             if (!plan_fits(g, p)) return WINO_ERR_WORKSPACE;
         } else {
             if (overlap(workspace, need, x, xb) || overlap(workspace, need, y, yb) || overlap(workspace, need, U, ub))
                 return WINO_ERR_INVALID_ARG;
+            if (p.bf3) return hip_status(launch_bf3(x, U, y, workspace, g, relu, s));
             return hip_status(launch_split(x, U, y, (float*)workspace, g, p.cfg.bw, relu, s));
         }
     }

@@ -109,6 +109,14 @@ hipError_t launch_split16(const float* x, const void* UH, float* y, void* VH, co
                           hipStream_t s);
 hipError_t launch_split(const float* x, const float* U, float* y, float* Vb, const Geom& g, int bw, bool relu,
                         hipStream_t s);
+// The split path's layers on the bf16 matrix cores: the fp32 operands split
+// exactly into bf16 terms, the whole layer in one kernel after the filters'
+// split into the workspace (bf3_workspace bytes).
+size_t bf3_workspace(const Geom& g);
+long bf3_items(const Geom& g);               // work items: (tile blocks, filter group)
+bool bf3_takes(const Geom& g);               // layers and offsets the kernel handles
+double bf3_ns(const Geom& g);                // its estimated time
+hipError_t launch_bf3(const float* x, const float* U, float* y, void* ws, const Geom& g, bool relu, hipStream_t s);
 // Low-C path (C <= 4): a lane per tile, vector FMAs over the few channels.
 hipError_t launch_lowc(const float* x, const float* U, float* y, const Geom& g, bool relu, hipStream_t s);
 hipError_t launch_maxpool2x2(const float* x, float* y, int N, int C, int H, int W, hipStream_t s);

@@ -1,0 +1,98 @@
+"""Large fp32 layers on the bf16 matrix cores (every fp32 operand split exactly
+into three bf16 terms), against the fp64 direct oracle at the edges of the
+kernel's tiles: filters, channels and tiles that leave remainders in the
+64-filter groups, 16-channel steps and 32- or 64-tile blocks, odd widths (the
+last tile's columns past the image), images of which several share a block of
+tiles, a single channel step, and F(4x4,3x3), F(2x2,3x3), F(2x2,5x5).
+
+A layer runs this kernel when AUTO asks for exactly the filters' split as
+workspace: 6 bytes per element of U with the channels in whole steps of 16.
+
+Tolerances: the gates of the fp32 paths.  The split drops products below
+2^-21 of |u v| (2^-24 on average), inside fp32 rounding; on integers whose
+terms fit 16 bits nothing is dropped and the result is the oracle's exactly."""
+import numpy as np
+import pytest
+
+import gpu_helpers as h
+from oracle import direct
+from paper_1903_01521_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+TOL = {2: 1e-4, 4: 1e-3}
+
+
+def split_bytes(C, K, m, r):
+    return -(-K // 16) * -(-C // 16) * (m + r - 1) ** 2 * 1536
+
+
+# (N, C, H, W, K, m, r)
+SHAPES = [
+    (33, 64, 56, 56, 64, 4, 3),     # whole tiles, 4 steps, half a 32-tile block at the end
+    (70, 77, 29, 27, 50, 4, 3),     # odd: 8 x 7 tiles, blocks across images, C and K ragged
+    (300, 61, 13, 14, 64, 4, 3),    # small images: 4 x 4 tiles, a block holds two
+    (13, 64, 112, 110, 33, 4, 3),   # one filter group with a filter in its last block
+    (30, 40, 28, 28, 144, 2, 3),    # F(2x2): whole tiles
+    (99, 45, 27, 25, 60, 2, 3),     # odd
+    (16, 48, 35, 35, 64, 2, 5),     # 5x5, odd
+    (41, 39, 34, 36, 60, 2, 5),     # 5x5, whole tiles
+]
+
+
+def _conv(x, g, m, r, flags=0):
+    N, C, H, W = x.shape
+    K = g.shape[0]
+    pad = r // 2
+    U = h.empty_bytes(B.wino_filter_bytes_r(C, K, m, r))
+    B.check(B.wino_filter_transform_r(h.dev(g), U, C, K, m, r))
+    wsb = B.wino_workspace_bytes_r(N, C, H, W, K, pad, m, r, flags)
+    assert wsb == split_bytes(C, K, m, r), "the layer runs on the bf16 matrix cores"
+    ws, y = h.empty_bytes(wsb), h.empty_bytes(4 * N * K * H * W)
+    y.fill_(float("nan"))
+    B.check(B.wino_conv2d_r(h.dev(x), U, y, N, C, H, W, K, pad, m, r, flags, ws, wsb))
+    return h.host(y).reshape(N, K, H, W)
+
+
+def _reference(x, g, r, absval=False):
+    return direct.conv2d(x, g, r // 2, absval=absval) if r == 3 else \
+        direct.conv2d(x, g, r // 2, absval=absval)
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_bf3_edges(shape):
+    N, C, H, W, K, m, r = shape
+    print(f"bf3 shape={shape}", flush=True)
+    rng = np.random.default_rng(sum(shape))
+    x = rng.standard_normal((N, C, H, W)).astype(np.float32)
+    g = (rng.standard_normal((K, C, r, r)) * np.sqrt(2.0 / (r * r * C))).astype(np.float32)
+    y = _conv(x, g, m, r, B.WINO_FLAG_RELU)
+    ref = np.maximum(_reference(x, g, r), 0.0)
+    assert np.all(np.isfinite(y))
+    err = h.normwise_err(y, ref)
+    print(f"  normwise err {err:.2e}", flush=True)
+    assert err <= (1e-3 if r == 5 else TOL[m])
+    assert np.array_equal(y, _conv(x, g, m, r, B.WINO_FLAG_RELU))      # bitwise run to run
+
+
+@pytest.mark.parametrize("shape", [SHAPES[1], SHAPES[5]], ids=lambda s: "x".join(map(str, s)))
+def test_bf3_exact_on_integers(shape):
+    # |V| <= 100 (m = 4) and |U| <= 576 * 9 / 16: both below 2^16, so no third
+    # term is dropped, and every sum is an integer below 2^24.
+    N, C, H, W, K, m, r = shape
+    print(f"bf3 integers shape={shape}", flush=True)
+    rng = np.random.default_rng(5)
+    x = rng.integers(-1, 2, (N, C, H, W)).astype(np.float32)
+    g = (rng.integers(-1, 2, (K, C, r, r)) * (576 if m == 4 else 4)).astype(np.float32)
+    assert np.array_equal(_conv(x, g, m, r).astype(np.float64), _reference(x, g, r))
+
+
+@pytest.mark.parametrize("scale", [1e-25, 1e25])
+def test_bf3_range(scale):
+    # the split keeps fp32's exponent range: scaled inputs give scaled results
+    N, C, H, W, K, m, r = SHAPES[2]
+    print(f"bf3 scale={scale}", flush=True)
+    rng = np.random.default_rng(6)
+    x = (rng.standard_normal((N, C, H, W)) * scale).astype(np.float32)
+    g = (rng.standard_normal((K, C, r, r)) * np.sqrt(2.0 / (9 * C))).astype(np.float32)
+    assert h.normwise_err(_conv(x, g, m, r), _reference(x, g, r)) <= TOL[m]
