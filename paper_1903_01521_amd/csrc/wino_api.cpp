@@ -102,7 +102,9 @@ struct Plan {
     bool automatic;       // chosen by the planner (split falls back to fused without workspace)
     FusedCfg cfg;
     bool bf3;             // on the bf16 matrix cores, the operands split exactly in three (launch_bf3)
-    size_t need;          // workspace of SPLIT, of FUSED with slices, and of bf3
+    size_t need;          // workspace of SPLIT, bf3 and g3
+    bool g3;              // the three stages with the GEMMs on the bf16 matrix cores (run_g3), in need3 bytes
+    size_t need3;
 };
 
 // Row groups per unit of the fused kernel: alpha = 4 (F(2x2,3x3)) keeps all
@@ -177,6 +179,24 @@ constexpr double kBf3Margin = 0.95;
 // 27 layers from 10 to 72 us lie above it at least).
 double fused_full_ns(const Geom& g, FusedCfg c) { return fused_ns(g, c) + 2500.0 * rounds(fused_workgroups(g, c)); }
 
+// The three stages' workspace: V and M, and for the GEMMs on the bf16 matrix
+// cores the split filters, the split V and M.
+size_t stage_bytes(const Geom& g) { return round_up(v_elems(g) * sizeof(float), 256) + m_elems(g) * sizeof(float); }
+size_t stage3_bytes(const Geom& g) {
+    return round_up(us_bytes(g), 256) + round_up(v3_bytes(g), 256) + m_elems(g) * sizeof(float);
+}
+
+// The three stages with the GEMMs on the bf16 matrix cores (1-D, NCHW or NHWC).
+hipError_t run_g3(const float* x, const float* U, float* y, void* ws, const Geom& g, bool relu, hipStream_t s) {
+    char* V = (char*)ws + round_up(us_bytes(g), 256);
+    float* M = (float*)(V + round_up(v3_bytes(g), 256));
+    hipError_t e = launch_usplit(U, ws, g, s);
+    if (e == hipSuccess) e = launch_input_transform3(x, V, g, s);
+    if (e == hipSuccess) e = launch_gemm3(ws, V, M, g, s);
+    if (e == hipSuccess) e = launch_output_transform(M, y, g, relu, s);
+    return e;
+}
+
 // Offsets into x that the NCHW input kernels form (see kInvalidOffset): one
 // image for the fused and split kernels; for the staged input transforms the
 // images one 16-tile block spans, at most 16 / (th*tw) + 2.
@@ -227,10 +247,40 @@ bool plan_fits(const Geom& g, const Plan& p) {
 
 int make_plan_unchecked(const Geom& g, unsigned flags, Plan* p);
 
+// Estimated times of the three stages: the transforms' bytes at the rates they
+// reach (4.8 and 5.6 TB/s), and the GEMMs, in fp32 at 105 TFLOP/s, or on the
+// bf16 matrix cores (g3) in rounds of one workgroup per CU, 2.1 us per 16-channel
+// step (the chip's clock falls to 1.6 GHz under them) and 3 us for M's stores,
+// after the filters' split.  g3 measured 249 us on the 32-image 512-channel
+// 28x28 layer (here 241) and 102 us at 14x14 with F(2x2) (here 112).
+double staged_ns(const Geom& g, bool g3) {
+    const double x = 4.0 * g.N * g.C * g.H * g.W, y = 4.0 * g.N * g.K * g.Ho * g.Wo, m = 4.0 * m_elems(g);
+    const double v = g3 ? (double)v3_bytes(g) : 4.0 * v_elems(g);
+    const double in = 2000.0 + (x + v) / 4800.0, out = 2000.0 + (m + y) / 5600.0;
+    if (!g3) return in + out + 2000.0 + 2.0 * g.T * g.P * (double)g.C * g.K / 105000.0;
+    const double steps = (g.CQ + 3) / 4, gemm = rounds(gemm3_items(g)) * (3000.0 + 2100.0 * steps);
+    return in + out + 1000.0 + 10.0 * 256.0 * g.T * g.KB * steps / 6000.0 + (gemm > (v + m) / 3200.0 ? gemm : (v + m) / 3200.0);
+}
+
+// AUTO's last choice: the three stages with the GEMMs on the bf16 matrix cores
+// (deep layers with few tiles: many filters to share a transformed input, so
+// that writing and reading V and M costs less than transforming again).
+void choose_g3(const Geom& g, unsigned flags, Plan* p) {
+    if (!p->automatic || p->algo == WINO_ALGO_LOWC || (flags & ~WINO_FLAG_RELU) || !gemm3_takes(g)) return;
+    if (g.axis == 0 && !g.nhwc && !block_images_fit(g)) return;
+    const double base = p->bf3 ? bf3_ns(g)
+                      : p->algo == WINO_ALGO_SPLIT ? split_ns(g)
+                      : p->algo == WINO_ALGO_STAGED ? staged_ns(g, false)
+                                                    : fused_full_ns(g, p->cfg);
+    if (staged_ns(g, true) >= 0.9 * base) return;
+    p->g3 = true;
+    p->need3 = stage3_bytes(g);
+}
+
 // The plan, or WINO_ERR_UNSUPPORTED where its input kernels' offsets would not
 // fit.  AUTO moves on to the next algorithm that fits: an unsliced fused plan
 // to split, then to the three stages.
-int make_plan(const Geom& g, unsigned flags, Plan* p) {
+int make_plan_base(const Geom& g, unsigned flags, Plan* p) {
     const int st = make_plan_unchecked(g, flags, p);
     if (st != WINO_OK || g.axis != 0 || g.nhwc) return st;
     if (prec_of(flags)) return prec_offsets_fit(g) ? WINO_OK : WINO_ERR_UNSUPPORTED;
@@ -249,6 +299,12 @@ int make_plan(const Geom& g, unsigned flags, Plan* p) {
     p->algo = WINO_ALGO_STAGED;
     p->cfg.nsl = 1;
     return plan_fits(g, *p) ? WINO_OK : WINO_ERR_UNSUPPORTED;
+}
+
+int make_plan(const Geom& g, unsigned flags, Plan* p) {
+    const int st = make_plan_base(g, flags, p);
+    if (st == WINO_OK) choose_g3(g, flags, p);
+    return st;
 }
 
 int make_plan_unchecked(const Geom& g, unsigned flags, Plan* p) {
@@ -280,6 +336,8 @@ int make_plan_unchecked(const Geom& g, unsigned flags, Plan* p) {
         p->cfg = FusedCfg{1, 16, 1};
         p->bf3 = false;
         p->need = 0;
+        p->g3 = false;
+        p->need3 = 0;
         // AUTO: split on layers with at least two full rounds of its items
         // (tile-block pair x filter group) on the CUs, where the saved M round
         // trip outweighs its per-item prologue and epilogue.
@@ -322,6 +380,8 @@ int make_plan_unchecked(const Geom& g, unsigned flags, Plan* p) {
     p->cfg = c;
     p->bf3 = false;
     p->need = 0;
+    p->g3 = false;
+    p->need3 = 0;
     // Layers with at most 4 channels: the low-C kernel.
     if (p->automatic && g.r == 3 && g.C <= 4 && !cs_req && !blk) {
         p->algo = WINO_ALGO_LOWC;
@@ -424,6 +484,7 @@ size_t wino_workspace_bytes_r(int N, int C, int H, int W, int K, int pad, int m,
         return (size_t)-1;
     if (prec_of(flags) && p.algo == WINO_ALGO_SPLIT) return split16_workspace(g);
     if (prec_of(flags)) return round_up(vh_bytes(g), 256) + m_elems(g) * sizeof(float);
+    if (p.g3) return p.need3;
     if (p.algo == WINO_ALGO_SPLIT || p.bf3) return p.need;
     if (p.algo == WINO_ALGO_FUSED && p.cfg.nsl > 1) return slice_workspace(g, p.cfg.nsl);
     if (p.algo == WINO_ALGO_FUSED || p.algo == WINO_ALGO_LOWC) return 0;
@@ -501,6 +562,11 @@ int wino_conv2d_r(const float* x, const float* U, float* y, int N, int C, int H,
         if (overlap(workspace, need, x, xb) || overlap(workspace, need, y, yb) || overlap(workspace, need, U, ub))
             return WINO_ERR_INVALID_ARG;
         return hip_status(launch_staged16(x, U, y, workspace, (float*)((char*)workspace + vb), g, prec, relu, s));
+    }
+    if (p.g3 && workspace && workspace_bytes >= p.need3) {
+        if (overlap(workspace, p.need3, x, xb) || overlap(workspace, p.need3, y, yb) || overlap(workspace, p.need3, U, ub))
+            return WINO_ERR_INVALID_ARG;
+        return hip_status(run_g3(x, U, y, workspace, g, relu, s));
     }
     if (p.algo == WINO_ALGO_SPLIT || p.bf3) {
         const size_t need = p.need;
@@ -649,7 +715,7 @@ size_t wino_workspace_bytes_1d(int N, int C, int H, int W, int K, int pad, int m
     Plan p;
     if (make_geom_1d(N, C, H, W, K, pad, m, r, axis, &g) != WINO_OK || make_plan(g, flags, &p) != WINO_OK)
         return (size_t)-1;
-    return round_up(v_elems(g) * sizeof(float), 256) + m_elems(g) * sizeof(float);
+    return p.g3 ? p.need3 : stage_bytes(g);
 }
 
 int wino_conv2d_1d(const float* x, const float* U, float* y, int N, int C, int H, int W, int K, int pad, int m,
@@ -666,11 +732,13 @@ int wino_conv2d_1d(const float* x, const float* U, float* y, int N, int C, int H
     const size_t ub = wino_filter_bytes_1d(C, K, m, r);
     if (overlap(x, xb, y, yb) || overlap(U, ub, y, yb)) return WINO_ERR_INVALID_ARG;
     const size_t vb = round_up(v_elems(g) * sizeof(float), 256);
-    const size_t need = vb + m_elems(g) * sizeof(float);
+    const bool g3 = p.g3 && workspace_bytes >= p.need3;
+    const size_t need = g3 ? p.need3 : stage_bytes(g);
     if (!workspace || workspace_bytes < need) return WINO_ERR_WORKSPACE;
     if (overlap(workspace, need, x, xb) || overlap(workspace, need, y, yb) || overlap(workspace, need, U, ub))
         return WINO_ERR_INVALID_ARG;
     hipStream_t s = (hipStream_t)stream;
+    if (g3) return hip_status(run_g3(x, U, y, workspace, g, (flags & WINO_FLAG_RELU) != 0, s));
     float* V = (float*)workspace;
     float* M = (float*)((char*)workspace + vb);
     st = hip_status(launch_input_transform(x, V, g, s));
@@ -686,8 +754,8 @@ size_t wino_workspace_bytes_nhwc(int N, int C, int H, int W, int K, int pad, int
     if (make_geom(N, C, H, W, K, pad, m, &g) != WINO_OK) return (size_t)-1;
     g.nhwc = 1;
     if (make_plan(g, flags, &p) != WINO_OK) return (size_t)-1;
-    if (p.algo == WINO_ALGO_SPLIT) return split_workspace(g);
-    return round_up(v_elems(g) * sizeof(float), 256) + m_elems(g) * sizeof(float);
+    if (p.g3) return p.need3;
+    return p.algo == WINO_ALGO_SPLIT ? split_workspace(g) : stage_bytes(g);
 }
 
 int wino_conv2d_nhwc(const float* x, const float* U, float* y, int N, int C, int H, int W, int K, int pad, int m,
@@ -705,6 +773,11 @@ int wino_conv2d_nhwc(const float* x, const float* U, float* y, int N, int C, int
     const size_t ub = wino_filter_bytes(C, K, m);
     if (overlap(x, xb, y, yb) || overlap(U, ub, y, yb)) return WINO_ERR_INVALID_ARG;
     hipStream_t s = (hipStream_t)stream;
+    if (p.g3 && workspace && workspace_bytes >= p.need3) {
+        if (overlap(workspace, p.need3, x, xb) || overlap(workspace, p.need3, y, yb) || overlap(workspace, p.need3, U, ub))
+            return WINO_ERR_INVALID_ARG;
+        return hip_status(run_g3(x, U, y, workspace, g, (flags & WINO_FLAG_RELU) != 0, s));
+    }
     if (p.algo == WINO_ALGO_SPLIT) {
         const size_t need = split_workspace(g);
         if (!workspace || workspace_bytes < need) return WINO_ERR_WORKSPACE;

@@ -22,18 +22,6 @@
 namespace wino {
 
 // ------------------------------------------------------------------ split U
-constexpr uint32_t kHi16 = 0xffff0000u;
-
-// (X, Y) of one value, h and m cut off: see above.
-__device__ __forceinline__ void split3(float v, uint32_t& X, uint32_t& Y) {
-    const uint32_t vb = __float_as_uint(v);
-    const float r1 = v - __uint_as_float(vb & kHi16);               // exact
-    const uint32_t rb = __float_as_uint(r1);
-    const float r2 = r1 - __uint_as_float(rb & kHi16);              // exact, at most 8 bits
-    X = __builtin_amdgcn_perm(vb, rb, 0x07060302u);                 // low half m, high half h
-    Y = __builtin_amdgcn_perm(__float_as_uint(r2), vb, 0x07060302u);   // low half h, high half l
-}
-
 // The same with h and m rounded to nearest (h only where that cannot
 // overflow): m and l then have either sign, so that the dropped products of
 // the filters' terms with an input's cut-off ones average out.
@@ -54,7 +42,6 @@ __device__ __forceinline__ void split3_rounded(float v, uint32_t& X, uint32_t& Y
 // through L2 and L1 once per workgroup, so their bytes are what counts.
 // Channels past C are zero (padding of U, or quads past CQ).  A thread does
 // four positions.
-constexpr int kUsBytes = 1536;                  // of one (filter block, 16 channels, position)
 __global__ __launch_bounds__(256) void k_usplit(const float* __restrict__ U, char* __restrict__ US, int CQ,
                                                 int C16, int TG, long n) {
     const long i = (long)blockIdx.x * 256 + threadIdx.x;
@@ -357,11 +344,7 @@ __global__ __launch_bounds__(512) void k_bf3(const float* __restrict__ x, const 
             if constexpr (b == 0) {
 #pragma unroll
                 for (int f = 0; f < FB; ++f) {
-                    const uint4 X = uX[p % D][f];
-                    const uint2 L = uL[p % D][f];
-                    uY[f] = make_uint4(
-                        __builtin_amdgcn_perm(L.x, X.x, 0x05040302u), __builtin_amdgcn_perm(L.x, X.y, 0x07060302u),
-                        __builtin_amdgcn_perm(L.y, X.z, 0x05040302u), __builtin_amdgcn_perm(L.y, X.w, 0x07060302u));
+                    uY[f] = us_y(uX[p % D][f], uL[p % D][f]);
                 }
             }
             slot(IC<p>{}, IC<3 * b>{});
@@ -454,7 +437,15 @@ __global__ __launch_bounds__(512) void k_bf3(const float* __restrict__ x, const 
 }
 
 // ------------------------------------------------------------------ host
-size_t bf3_workspace(const Geom& g) { return (size_t)g.KB * ((g.CQ + 3) / 4) * g.T * kUsBytes; }
+hipError_t launch_usplit(const float* U, void* US, const Geom& g, hipStream_t s) {
+    const int c16 = (g.CQ + 3) / 4, tg = g.T / 4;
+    const long n = (long)g.KB * c16 * tg * 64;
+    if ((n + 255) / 256 > 0x7fffffffL) return hipErrorInvalidConfiguration;
+    hipLaunchKernelGGL(k_usplit, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, U, (char*)US, g.CQ, c16, tg, n);
+    return hipGetLastError();
+}
+
+size_t bf3_workspace(const Geom& g) { return us_bytes(g); }
 
 long bf3_items(const Geom& g) {
     const long nb = ((long)g.P + 15) / 16, tb = g.A == 6 ? 2 : 4;
@@ -487,10 +478,8 @@ template <int MT, int R>
 static hipError_t bf3_instance(const float* x, const float* U, float* y, void* ws, const Geom& g, bool relu,
                                hipStream_t s) {
     using S = Bf3Shape<MT, R>;
-    const int c16 = (g.CQ + 3) / 4, tg = S::T / 4;
-    const long n = (long)g.KB * c16 * tg * 64;
-    hipLaunchKernelGGL(k_usplit, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, U, (char*)ws, g.CQ, c16, tg, n);
-    const hipError_t e = hipGetLastError();
+    const int c16 = (g.CQ + 3) / 4;
+    const hipError_t e = launch_usplit(U, ws, g, s);
     if (e != hipSuccess) return e;
     FusedTiling ft{};
     const int nb = (int)(((long)g.P + 15) / 16);

@@ -31,6 +31,74 @@ __device__ __forceinline__ f32x4 mfma16x16x32(uint4 a, uint4 b, f32x4 c) {
                                                         __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
+// ------------------------------------------------------------------ exact split
+// A fp32 value as three bf16 terms, h + m + l, eight significand bits each: the
+// operands of the kernels that run fp32 products on the bf16 matrix cores.
+constexpr uint32_t kHi16 = 0xffff0000u;
+
+// (X, Y) of one value, h and m cut off towards zero; low half first:
+// X = (m, h), Y = (h, l).
+__device__ __forceinline__ void split3(float v, uint32_t& X, uint32_t& Y) {
+    const uint32_t vb = __float_as_uint(v);
+    const float r1 = v - __uint_as_float(vb & kHi16);               // exact
+    const uint32_t rb = __float_as_uint(r1);
+    const float r2 = r1 - __uint_as_float(rb & kHi16);              // exact, at most 8 bits
+    X = __builtin_amdgcn_perm(vb, rb, 0x07060302u);                 // low half m, high half h
+    Y = __builtin_amdgcn_perm(__float_as_uint(r2), vb, 0x07060302u);   // low half h, high half l
+}
+
+// 4 x 4 transpose of the wave's four rows of 16 lanes and four registers: r[k]
+// in row e becomes r[e] of row k.
+__device__ __forceinline__ void transpose_rows(uint32_t (&r)[4]) {
+    auto swap32 = [](uint32_t& a, uint32_t& b) {       // rows 2, 3 of a with rows 0, 1 of b
+        const auto q = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+        a = q[0];
+        b = q[1];
+    };
+    auto swap16 = [](uint32_t& a, uint32_t& b) {       // rows 1, 3 of a with rows 0, 2 of b
+        const auto q = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+        a = q[0];
+        b = q[1];
+    };
+    swap32(r[0], r[2]);
+    swap32(r[1], r[3]);
+    swap16(r[0], r[1]);
+    swap16(r[2], r[3]);
+}
+
+// Split filters in memory (k_usplit): per (filter block, 16 channels, position)
+// the X words [64][16 bytes] and the l terms [64][8 bytes].
+constexpr int kUsBytes = 1536;
+
+// The same layout for transformed inputs, [tile block][C16][T]{X, l}: a wave
+// that holds T values of (channel lane / 16 of quad q, tile lane % 16) stores
+// them as operand words, four positions at a time (after the transpose a lane
+// has the quad's four channels at position lane / 16).  blk: the (tile block, 16
+// channels).  Whole columns of lanes (one tile's four) are active or not.
+template <int T>
+__device__ __forceinline__ void store_v3(char* __restrict__ blk, int q, int lane, const float (&v)[T]) {
+    char* p = blk + (lane >> 4) * kUsBytes;
+    const int i = q * 16 + (lane & 15);
+#pragma unroll
+    for (int g4 = 0; g4 < T / 4; ++g4) {
+        uint32_t r[4], X[4], Y[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) r[e] = __float_as_uint(v[4 * g4 + e]);
+        transpose_rows(r);
+#pragma unroll
+        for (int d = 0; d < 4; ++d) split3(__uint_as_float(r[d]), X[d], Y[d]);
+        *(uint4*)(p + g4 * 4 * kUsBytes + i * 16) = make_uint4(X[0], X[1], X[2], X[3]);
+        *(uint2*)(p + g4 * 4 * kUsBytes + 1024 + i * 8) = make_uint2(__builtin_amdgcn_perm(Y[1], Y[0], 0x07060302u),
+                                                                     __builtin_amdgcn_perm(Y[3], Y[2], 0x07060302u));
+    }
+}
+
+// A lane's Y = (h, l) words from its X = (m, h) words and l terms.
+__device__ __forceinline__ uint4 us_y(uint4 X, uint2 L) {
+    return make_uint4(__builtin_amdgcn_perm(L.x, X.x, 0x05040302u), __builtin_amdgcn_perm(L.x, X.y, 0x07060302u),
+                      __builtin_amdgcn_perm(L.y, X.z, 0x05040302u), __builtin_amdgcn_perm(L.y, X.w, 0x07060302u));
+}
+
 // ------------------------------------------------------------------ helpers
 
 __device__ __forceinline__ uint32_t fdiv(uint32_t n, FastDiv d) { return (__umulhi(n, d.m) + n) >> d.l; }

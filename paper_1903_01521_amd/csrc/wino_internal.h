@@ -117,6 +117,15 @@ long bf3_items(const Geom& g);               // work items: (tile blocks, filter
 bool bf3_takes(const Geom& g);               // layers and offsets the kernel handles
 double bf3_ns(const Geom& g);                // its estimated time
 hipError_t launch_bf3(const float* x, const float* U, float* y, void* ws, const Geom& g, bool relu, hipStream_t s);
+// The stages of large layers on the bf16 matrix cores, U and V as split operand
+// words (us_bytes, v3_bytes) and M in fp32.
+size_t us_bytes(const Geom& g);
+size_t v3_bytes(const Geom& g);
+hipError_t launch_usplit(const float* U, void* US, const Geom& g, hipStream_t s);
+hipError_t launch_input_transform3(const float* x, void* V3, const Geom& g, hipStream_t s);
+bool gemm3_takes(const Geom& g);
+long gemm3_items(const Geom& g);
+hipError_t launch_gemm3(const void* US, const void* V3, float* M, const Geom& g, hipStream_t s);
 // Low-C path (C <= 4): a lane per tile, vector FMAs over the few channels.
 hipError_t launch_lowc(const float* x, const float* U, float* y, const Geom& g, bool relu, hipStream_t s);
 hipError_t launch_maxpool2x2(const float* x, float* y, int N, int C, int H, int W, hipStream_t s);

@@ -109,15 +109,17 @@ __global__ __launch_bounds__(256) void k_filter(const float* __restrict__ gw, fl
 // neighbouring tile blocks so their overlapping regions share cache lines, and
 // each XCD takes one contiguous run of workgroups (workgroup b runs item
 // (b % 8) * per + b / 8), so those neighbours meet in the same L2.
-template <int MT, int R = 3>
+// V3: into split operand words (store_v3), nq quads per block (CQ, or for V3 CQ
+// rounded up to 4: the padding quads are zeros).
+template <int MT, int R = 3, bool V3 = false>
 __global__ __launch_bounds__(256) void k_input(const float* __restrict__ x, float* __restrict__ V, Geom g,
-                                               long nwg) {
+                                               long nwg, int nq) {
     constexpr int A = MT + R - 1, T = A * A;
     const int lane = threadIdx.x & 63;
     const long per = (nwg + 7) / 8, item = (long)(blockIdx.x % 8) * per + blockIdx.x / 8;
     if (item >= nwg) return;
     const long w = item * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (w >= (long)g.PB * g.CQ) return;
+    if (w >= (long)g.PB * nq) return;
     const int cq = (int)(w / g.PB), pb = (int)(w % g.PB);
     const int cl = lane >> 4;
     const TileCoord tc = decode_tile(pb * 16 + (lane & 15), g);
@@ -126,7 +128,8 @@ __global__ __launch_bounds__(256) void k_input(const float* __restrict__ x, floa
     load_region<MT, A>(rp, g, cq, cl, d);
     float v[T];
     input_tf<A - 2>(d, v);                 // B^T depends only on the region side (the points)
-    store_t4<T, true>(V + ((size_t)pb * g.CQ + cq) * T * 64, lane, v);
+    if constexpr (V3) store_v3<T>((char*)V + ((size_t)pb * (nq >> 2) + (cq >> 2)) * T * kUsBytes, cq & 3, lane, v);
+    else store_t4<T, true>(V + ((size_t)pb * g.CQ + cq) * T * 64, lane, v);
 }
 
 // ------------------------------------------------------------------ output
@@ -1122,7 +1125,9 @@ __global__ __launch_bounds__(256) void k_vrows(const float* __restrict__ x, floa
             }
             float v[T];
             input_tf<MT>(d, v);
-            if constexpr (OUT == 0) {
+            if constexpr (OUT == 3) {
+                store_v3<T>((char*)Vb + ((size_t)blk * (nq >> 2) + (cq >> 2)) * T * kUsBytes, cq & 3, lane, v);
+            } else if constexpr (OUT == 0) {
 #pragma unroll
                 for (int g4 = 0; g4 < T / 4; ++g4)
                     store_out<false>(dst + g4 * 256, v[4 * g4], v[4 * g4 + 1], v[4 * g4 + 2], v[4 * g4 + 3]);
@@ -1132,7 +1137,10 @@ __global__ __launch_bounds__(256) void k_vrows(const float* __restrict__ x, floa
                 for (int t = 0; t < T; ++t) h[t * 256] = (unsigned short)to16<OUT>(v[t]);
             }
         } else if (last_tail && p >= g.P) {
-            if constexpr (OUT == 0) {
+            if constexpr (OUT == 3) {
+                const float z[T] = {};
+                store_v3<T>((char*)Vb + ((size_t)blk * (nq >> 2) + (cq >> 2)) * T * kUsBytes, cq & 3, lane, z);
+            } else if constexpr (OUT == 0) {
 #pragma unroll
                 for (int g4 = 0; g4 < T / 4; ++g4) store_out<false>(dst + g4 * 256, 0.f, 0.f, 0.f, 0.f);
             } else {
@@ -2126,7 +2134,7 @@ hipError_t launch_staged16(const float* x, const void* UH, float* y, void* VH, f
 // tile read 16 contiguous bytes per pixel).  Output (three stages): one wave
 // per (16-tile block, 16-filter block); a lane holds its tile's four
 // consecutive filters, so every output pixel is one 16-byte store.
-template <int MT>
+template <int MT, bool V3 = false>
 __global__ __launch_bounds__(256) void k_input_nhwc(const float* __restrict__ x, float* __restrict__ V, Geom g,
                                                     long nwg, int nq) {
     constexpr int A = MT + 2, T = A * A;
@@ -2154,7 +2162,8 @@ __global__ __launch_bounds__(256) void k_input_nhwc(const float* __restrict__ x,
         }
     float vv[T];
     input_tf<MT>(d, vv);
-    store_t4<T, true>(V + ((size_t)pb * nq + cq) * T * 64, lane, vv);
+    if constexpr (V3) store_v3<T>((char*)V + ((size_t)pb * (nq >> 2) + (cq >> 2)) * T * kUsBytes, cq & 3, lane, vv);
+    else store_t4<T, true>(V + ((size_t)pb * nq + cq) * T * 64, lane, vv);
 }
 
 // With C % 4 == 0 a channel quad of a pixel is one aligned 16-byte word: one
@@ -2230,7 +2239,7 @@ __global__ __launch_bounds__(256) void k_input_nhwc4(const float* __restrict__ x
 // zeros.  Offsets are 32-bit from the first image the rows touch (the host
 // checks that they fit below kInvalid).  Plain stores: the blocks two
 // workgroups share meet in L2 (streaming stores measured 1.7x slower).
-template <int MT>
+template <int MT, bool V3 = false>
 __global__ __launch_bounds__(256) void k_vrows_nhwc(const float* __restrict__ x, float* __restrict__ V, Geom g,
                                                     int R, int lqg, int QGP, int pitch, int nq, int nitems) {
     constexpr int A = MT + 2, T = A * A;
@@ -2298,9 +2307,16 @@ __global__ __launch_bounds__(256) void k_vrows_nhwc(const float* __restrict__ x,
                 for (int v = 0; v < A; ++v) d[u][v] = wp[(u * pitch + v) * QGP];
             float vv[T];
             input_tf<MT>(d, vv);
+            if constexpr (V3) {
+                store_v3<T>((char*)V + ((size_t)blk * (nq >> 2) + ((q0 + q) >> 2)) * T * kUsBytes, (q0 + q) & 3, lane, vv);
+            } else {
 #pragma unroll
-            for (int g4 = 0; g4 < T / 4; ++g4)
-                store_out<false>(dst + g4 * 256, vv[4 * g4], vv[4 * g4 + 1], vv[4 * g4 + 2], vv[4 * g4 + 3]);
+                for (int g4 = 0; g4 < T / 4; ++g4)
+                    store_out<false>(dst + g4 * 256, vv[4 * g4], vv[4 * g4 + 1], vv[4 * g4 + 2], vv[4 * g4 + 3]);
+            }
+        } else if (V3 && last_tail && p >= g.P) {
+            const float z[T] = {};
+            store_v3<T>((char*)V + ((size_t)blk * (nq >> 2) + ((q0 + q) >> 2)) * T * kUsBytes, (q0 + q) & 3, lane, z);
         } else if (last_tail && p >= g.P) {
 #pragma unroll
             for (int g4 = 0; g4 < T / 4; ++g4) store_out<false>(dst + g4 * 256, 0.f, 0.f, 0.f, 0.f);
@@ -2360,14 +2376,14 @@ __global__ __launch_bounds__(256) void k_filter1d(const float* __restrict__ gw, 
 // One wave per (16-tile block, 4-channel quad), XCD-contiguous runs as in
 // k_input; lane = (tile p%16, channel c%4) loads its 8 inputs along the axis
 // (zero outside the image, past C and past P) and writes B^T d.
-template <int MT, int AX>
+template <int MT, int AX, bool V3 = false>
 __global__ __launch_bounds__(256) void k_input1d(const float* __restrict__ x, float* __restrict__ V, Geom g,
-                                                 long nwg) {
+                                                 long nwg, int nq) {
     const int lane = threadIdx.x & 63;
     const long per = (nwg + 7) / 8, item = (long)(blockIdx.x % 8) * per + blockIdx.x / 8;
     if (item >= nwg) return;
     const long w = item * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (w >= (long)g.PB * g.CQ) return;
+    if (w >= (long)g.PB * nq) return;
     const int cq = (int)(w / g.PB), pb = (int)(w % g.PB);
     const TileCoord tc = decode_tile(pb * 16 + (lane & 15), g);
     const int c = cq * 4 + (lane >> 4);
@@ -2389,7 +2405,8 @@ __global__ __launch_bounds__(256) void k_input1d(const float* __restrict__ x, fl
     }
     float v[8];
     bt8(d, v);
-    store_t4<8, true>(V + ((size_t)pb * g.CQ + cq) * 8 * 64, lane, v);
+    if constexpr (V3) store_v3<8>((char*)V + ((size_t)pb * (nq >> 2) + (cq >> 2)) * 8 * kUsBytes, cq & 3, lane, v);
+    else store_t4<8, true>(V + ((size_t)pb * g.CQ + cq) * 8 * 64, lane, v);
 }
 
 // One wave per (16-tile block, 16-filter block): lane = (tile p%16, filter
@@ -2442,12 +2459,14 @@ hipError_t launch_filter_transform_1d(const float* gw, float* U, int C, int K, i
     return hipGetLastError();
 }
 
+template <bool V3>
 static hipError_t launch_input_1d(const float* x, float* V, const Geom& g, hipStream_t s) {
-    const long waves = (long)g.PB * g.CQ, nwg = (waves + 3) / 4;
+    const int nq = V3 ? (g.CQ + 3) / 4 * 4 : g.CQ;
+    const long waves = (long)g.PB * nq, nwg = (waves + 3) / 4;
     if ((nwg + 7) / 8 * 8 > 0x7fffffffL) return hipErrorInvalidConfiguration;
     const dim3 grid((unsigned)((nwg + 7) / 8 * 8)), block(256);
 #define WINO_IN1D(MT, AX) \
-    if (g.m == MT && g.axis == AX) { hipLaunchKernelGGL((k_input1d<MT, AX>), grid, block, 0, s, x, V, g, nwg); return hipGetLastError(); }
+    if (g.m == MT && g.axis == AX) { hipLaunchKernelGGL((k_input1d<MT, AX, V3>), grid, block, 0, s, x, V, g, nwg, nq); return hipGetLastError(); }
     WINO_IN1D(6, 1) WINO_IN1D(4, 1) WINO_IN1D(2, 1) WINO_IN1D(6, 2) WINO_IN1D(4, 2) WINO_IN1D(2, 2)
 #undef WINO_IN1D
     return hipErrorInvalidValue;
@@ -2556,6 +2575,7 @@ static NhwcRowsPlan nhwc_rows_plan(const Geom& g, int nq) {
 
 // Channel-last input transform into V blocks of nq quads ([PB][nq][T/4][64][4]:
 // nq = CQ for the three stages, CQ rounded up to 4 for the split path).
+template <bool V3 = false>
 static hipError_t launch_input_nhwc(const float* x, float* V, const Geom& g, int nq, hipStream_t s) {
     const dim3 block(256);
     if (g.C % 4 == 0 && aligned(x, 16)) {
@@ -2564,10 +2584,10 @@ static hipError_t launch_input_nhwc(const float* x, float* V, const Geom& g, int
             const int nitems = (int)(((long)g.N * g.th + rp.R - 1) / rp.R * ((nq + (1 << rp.lqg) - 1) >> rp.lqg));
             const dim3 grid((unsigned)((nitems + 7) / 8 * 8));
             if (g.m == 2)
-                hipLaunchKernelGGL(k_vrows_nhwc<2>, grid, block, rp.lds, s, x, V, g, rp.R, rp.lqg, rp.QGP, rp.pitch,
+                hipLaunchKernelGGL((k_vrows_nhwc<2, V3>), grid, block, rp.lds, s, x, V, g, rp.R, rp.lqg, rp.QGP, rp.pitch,
                                    nq, nitems);
             else
-                hipLaunchKernelGGL(k_vrows_nhwc<4>, grid, block, rp.lds, s, x, V, g, rp.R, rp.lqg, rp.QGP, rp.pitch,
+                hipLaunchKernelGGL((k_vrows_nhwc<4, V3>), grid, block, rp.lds, s, x, V, g, rp.R, rp.lqg, rp.QGP, rp.pitch,
                                    nq, nitems);
             return hipGetLastError();
         }
@@ -2580,24 +2600,26 @@ static hipError_t launch_input_nhwc(const float* x, float* V, const Geom& g, int
     // stay below kInvalid
     const size_t img_b = (size_t)g.H * g.W * g.C * 4;
     const size_t span = (size_t)(16 / (g.th * g.tw) + 2);
-    if (g.C % 4 == 0 && aligned(x, 16) && span * img_b < (size_t)kInvalid) {
+    if (!V3 && g.C % 4 == 0 && aligned(x, 16) && span * img_b < (size_t)kInvalid) {
         const int CG = (nq + 3) / 4;
         const long nwg4 = ((long)g.PB * CG + 3) / 4;
         const dim3 grid4((unsigned)((nwg4 + 7) / 8 * 8));
         if (g.m == 2) hipLaunchKernelGGL(k_input_nhwc4<2>, grid4, block, 0, s, x, V, g, CG, nwg4, nq);
         else hipLaunchKernelGGL(k_input_nhwc4<4>, grid4, block, 0, s, x, V, g, CG, nwg4, nq);
     } else if (g.m == 2) {
-        hipLaunchKernelGGL(k_input_nhwc<2>, grid, block, 0, s, x, V, g, nwg, nq);
+        hipLaunchKernelGGL((k_input_nhwc<2, V3>), grid, block, 0, s, x, V, g, nwg, nq);
     } else {
-        hipLaunchKernelGGL(k_input_nhwc<4>, grid, block, 0, s, x, V, g, nwg, nq);
+        hipLaunchKernelGGL((k_input_nhwc<4, V3>), grid, block, 0, s, x, V, g, nwg, nq);
     }
     return hipGetLastError();
 }
 
-hipError_t launch_input_transform(const float* x, float* V, const Geom& g, hipStream_t s) {
-    if (g.axis != 0) return launch_input_1d(x, V, g, s);
-    if (g.nhwc) return launch_input_nhwc(x, V, g, g.CQ, s);
-    const long waves = (long)g.PB * g.CQ, nwg = (waves + 3) / 4;
+template <bool V3>
+static hipError_t input_transform(const float* x, float* V, const Geom& g, hipStream_t s) {
+    const int nq = V3 ? (g.CQ + 3) / 4 * 4 : g.CQ;
+    if (g.axis != 0) return launch_input_1d<V3>(x, V, g, s);
+    if (g.nhwc) return launch_input_nhwc<V3>(x, V, g, nq, s);
+    const long waves = (long)g.PB * nq, nwg = (waves + 3) / 4;
     if ((nwg + 7) / 8 * 8 > 0x7fffffffL) return hipErrorInvalidConfiguration;
     const dim3 grid((unsigned)((nwg + 7) / 8 * 8)), block(256);
     if (g.r == 3) {
@@ -2606,19 +2628,28 @@ hipError_t launch_input_transform(const float* x, float* V, const Geom& g, hipSt
         const VrowsPlan vp = vrows_plan(g, vec);
         if (vp.R > 0) {
             const long ngr = ((long)g.N * g.th + vp.R - 1) / vp.R;
-            const dim3 gr((unsigned)(ngr * g.CQ)), b256(256);
-            if (g.m == 2) hipLaunchKernelGGL((k_vrows<2>), gr, b256, vp.lds, s, x, V, g, vp.R, vp.pitch, g.CQ);
-            else hipLaunchKernelGGL((k_vrows<4>), gr, b256, vp.lds, s, x, V, g, vp.R, vp.pitch, g.CQ);
+            const dim3 gr((unsigned)(ngr * nq)), b256(256);
+            constexpr int OUT = V3 ? 3 : 0;
+            if (g.m == 2) hipLaunchKernelGGL((k_vrows<2, OUT>), gr, b256, vp.lds, s, x, V, g, vp.R, vp.pitch, nq);
+            else hipLaunchKernelGGL((k_vrows<4, OUT>), gr, b256, vp.lds, s, x, V, g, vp.R, vp.pitch, nq);
             return hipGetLastError();
         }
     }
     if (g.r == 5)
-        hipLaunchKernelGGL((k_input<2, 5>), grid, block, 0, s, x, V, g, nwg);
+        hipLaunchKernelGGL((k_input<2, 5, V3>), grid, block, 0, s, x, V, g, nwg, nq);
     else if (g.m == 2)
-        hipLaunchKernelGGL(k_input<2>, grid, block, 0, s, x, V, g, nwg);
+        hipLaunchKernelGGL((k_input<2, 3, V3>), grid, block, 0, s, x, V, g, nwg, nq);
     else
-        hipLaunchKernelGGL(k_input<4>, grid, block, 0, s, x, V, g, nwg);
+        hipLaunchKernelGGL((k_input<4, 3, V3>), grid, block, 0, s, x, V, g, nwg, nq);
     return hipGetLastError();
+}
+
+hipError_t launch_input_transform(const float* x, float* V, const Geom& g, hipStream_t s) {
+    return input_transform<false>(x, V, g, s);
+}
+
+hipError_t launch_input_transform3(const float* x, void* V3, const Geom& g, hipStream_t s) {
+    return input_transform<true>(x, (float*)V3, g, s);
 }
 
 hipError_t launch_batched_gemm(const float* U, const float* V, float* M, const Geom& g, hipStream_t s) {
