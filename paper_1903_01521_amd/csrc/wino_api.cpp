@@ -268,6 +268,7 @@ double staged_ns(const Geom& g, bool g3) {
 void choose_g3(const Geom& g, unsigned flags, Plan* p) {
     if (!p->automatic || p->algo == WINO_ALGO_LOWC || (flags & ~WINO_FLAG_RELU) || !gemm3_takes(g)) return;
     if (g.axis == 0 && !g.nhwc && !block_images_fit(g)) return;
+    if (p->algo == WINO_ALGO_FUSED && (p->cfg.csplit > 1 || p->cfg.nsl > 1)) return;   // rounds less often
     const double base = p->bf3 ? bf3_ns(g)
                       : p->algo == WINO_ALGO_SPLIT ? split_ns(g)
                       : p->algo == WINO_ALGO_STAGED ? staged_ns(g, false)
@@ -395,7 +396,11 @@ int make_plan_unchecked(const Geom& g, unsigned flags, Plan* p) {
         p->bf3 = p->automatic && bf3_takes(g) && bf3_workspace(g) <= p->need && bf3_ns(g) < kBf3Margin * split_ns(g);
         return WINO_OK;
     }
-    if (p->automatic && !cs_req && !blk && bf3_takes(g) && bf3_ns(g) < kBf3Margin * fused_full_ns(g, c)) {
+    // Not where the fused kernel splits the channels over waves: summed in parts
+    // it rounds less often than one chain of three bf16 products per 16
+    // channels (1.6e-6 against 1.8e-6 from the exact result at 112 channels,
+    // F(4x4); unsplit 2.0e-6).
+    if (p->automatic && !cs_req && !blk && c.csplit == 1 && bf3_takes(g) && bf3_ns(g) < kBf3Margin * fused_full_ns(g, c)) {
         p->bf3 = true;
         p->need = bf3_workspace(g);
         return WINO_OK;

@@ -32,9 +32,9 @@ SHAPES = [
     (33, 64, 56, 56, 64, 4, 3),     # whole tiles, 4 steps, half a 32-tile block at the end
     (70, 77, 29, 27, 50, 4, 3),     # odd: 8 x 7 tiles, blocks across images, C and K ragged
     (300, 61, 13, 14, 64, 4, 3),    # small images: 4 x 4 tiles, a block holds two
-    (13, 64, 112, 110, 33, 4, 3),   # one filter group with a filter in its last block
+    (20, 45, 112, 110, 49, 4, 3),   # one filter in the last block
     (30, 40, 28, 28, 144, 2, 3),    # F(2x2): whole tiles
-    (99, 45, 27, 25, 60, 2, 3),     # odd
+    (31, 37, 27, 25, 140, 2, 3),    # odd
     (16, 48, 35, 35, 64, 2, 5),     # 5x5, odd
     (41, 39, 34, 36, 60, 2, 5),     # 5x5, whole tiles
 ]
