@@ -131,8 +131,8 @@ extern "C" {
  * WINO_CSLICES(1) keeps AUTO from slicing. */
 #define WINO_CSLICES(n)    (((unsigned)(n) & 0xFu) << 20)
 
-/* WINO_ALGO_AUTO runs large fp32 "same" layers (pad (r-1)/2, NCHW) on the bf16
- * matrix cores: U and V are split exactly into three bf16 terms each (24
+/* WINO_ALGO_AUTO runs large fp32 "same" layers (pad (r-1)/2, NCHW), deep ones
+ * (also channel-last) and most 1-D ones on the bf16 matrix cores: U and V are split exactly into three bf16 terms each (24
  * significand bits, the whole fp32 exponent range) and the six largest of the
  * nine products are summed in fp32, for 2.67 times the fp32 matrix rate.  The
  * dropped products are below 2^-21 of |u v|; errors against 64 bits are no

@@ -13,7 +13,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libwino.so")
-KERNELS = [os.path.join(CSRC, f) for f in ("wino_kernels.hip", "wino_bf3.hip", "wino_gemm3.hip")]
+KERNELS = [os.path.join(CSRC, f) for f in ("wino_kernels.hip", "wino_bf3.hip", "wino_bf3_1d.hip", "wino_gemm3.hip")]
 SOURCES = KERNELS + [os.path.join(CSRC, "wino_api.cpp")]
 HEADERS = [os.path.join(CSRC, f) for f in ("wino_device.h", "wino_transforms.h", "wino_internal.h")] + [
     os.path.join(ROOT, "include", "wino.h")]

@@ -101,7 +101,7 @@ struct Plan {
     unsigned algo;        // WINO_ALGO_FUSED, WINO_ALGO_SPLIT or WINO_ALGO_STAGED
     bool automatic;       // chosen by the planner (split falls back to fused without workspace)
     FusedCfg cfg;
-    bool bf3;             // on the bf16 matrix cores, the operands split exactly in three (launch_bf3)
+    bool bf3;             // on the bf16 matrix cores, the operands split exactly in three (launch_bf3, launch_bf3_1d)
     size_t need;          // workspace of SPLIT, bf3 and g3
     bool g3;              // the three stages with the GEMMs on the bf16 matrix cores (run_g3), in need3 bytes
     size_t need3;
@@ -186,7 +186,7 @@ size_t stage3_bytes(const Geom& g) {
     return round_up(us_bytes(g), 256) + round_up(v3_bytes(g), 256) + m_elems(g) * sizeof(float);
 }
 
-// The three stages with the GEMMs on the bf16 matrix cores (1-D, NCHW or NHWC).
+// The three stages with the GEMMs on the bf16 matrix cores (NCHW or NHWC).
 hipError_t run_g3(const float* x, const float* U, float* y, void* ws, const Geom& g, bool relu, hipStream_t s) {
     char* V = (char*)ws + round_up(us_bytes(g), 256);
     float* M = (float*)(V + round_up(v3_bytes(g), 256));
@@ -266,8 +266,8 @@ double staged_ns(const Geom& g, bool g3) {
 // (deep layers with few tiles: many filters to share a transformed input, so
 // that writing and reading V and M costs less than transforming again).
 void choose_g3(const Geom& g, unsigned flags, Plan* p) {
-    if (!p->automatic || p->algo == WINO_ALGO_LOWC || (flags & ~WINO_FLAG_RELU) || !gemm3_takes(g)) return;
-    if (g.axis == 0 && !g.nhwc && !block_images_fit(g)) return;
+    if (!p->automatic || g.axis != 0 || p->algo == WINO_ALGO_LOWC || (flags & ~WINO_FLAG_RELU) || !gemm3_takes(g)) return;
+    if (!g.nhwc && !block_images_fit(g)) return;
     if (p->algo == WINO_ALGO_FUSED && (p->cfg.csplit > 1 || p->cfg.nsl > 1)) return;   // rounds less often
     const double base = p->bf3 ? bf3_ns(g)
                       : p->algo == WINO_ALGO_SPLIT ? split_ns(g)
@@ -276,6 +276,22 @@ void choose_g3(const Geom& g, unsigned flags, Plan* p) {
     if (staged_ns(g, true) >= 0.9 * base) return;
     p->g3 = true;
     p->need3 = stage3_bytes(g);
+}
+
+// AUTO's choice for 1-D layers: the one kernel on the bf16 matrix cores where it
+// is estimated 15% shorter than the three stages, whose workspace holds the
+// filters' split.  The stages of 16 layers took 14.5 us of launches and
+// latencies, the transforms' bytes, and GEMMs at 105 TFLOP/s or 0.8 us per
+// 16-channel step where few workgroups run.  With few tiles and many channels
+// they win (N = 1 192-channel 17x17: 22 against 30 us), as the one kernel's steps
+// take 2 us each; else the one kernel (N = 3 33 -> 50 at 101x37: 22 -> 15 us).
+bool choose_bf3_1d(const Geom& g, const Plan& p) {
+    if (!p.automatic || g.axis == 0 || !bf3_1d_takes(g) || us_bytes(g) > stage_bytes(g)) return false;
+    const double x = 4.0 * g.N * g.C * g.H * g.W, y = 4.0 * g.N * g.K * g.Ho * g.Wo;
+    const double gemm = 2.0 * g.T * g.P * (double)g.C * g.K / 105000.0, chain = 800.0 * ((g.CQ + 3) / 4);
+    const double stages = 14500.0 + (x + 4.0 * v_elems(g)) / 4800.0 + (4.0 * m_elems(g) + y) / 5600.0 +
+                          (gemm > chain ? gemm : chain);
+    return bf3_1d_ns(g) < 0.85 * stages;
 }
 
 // The plan, or WINO_ERR_UNSUPPORTED where its input kernels' offsets would not
@@ -305,6 +321,7 @@ int make_plan_base(const Geom& g, unsigned flags, Plan* p) {
 int make_plan(const Geom& g, unsigned flags, Plan* p) {
     const int st = make_plan_base(g, flags, p);
     if (st == WINO_OK) choose_g3(g, flags, p);
+    if (st == WINO_OK && choose_bf3_1d(g, *p)) p->bf3 = true;
     return st;
 }
 
@@ -720,7 +737,7 @@ size_t wino_workspace_bytes_1d(int N, int C, int H, int W, int K, int pad, int m
     Plan p;
     if (make_geom_1d(N, C, H, W, K, pad, m, r, axis, &g) != WINO_OK || make_plan(g, flags, &p) != WINO_OK)
         return (size_t)-1;
-    return p.g3 ? p.need3 : stage_bytes(g);
+    return stage_bytes(g);
 }
 
 int wino_conv2d_1d(const float* x, const float* U, float* y, int N, int C, int H, int W, int K, int pad, int m,
@@ -737,13 +754,12 @@ int wino_conv2d_1d(const float* x, const float* U, float* y, int N, int C, int H
     const size_t ub = wino_filter_bytes_1d(C, K, m, r);
     if (overlap(x, xb, y, yb) || overlap(U, ub, y, yb)) return WINO_ERR_INVALID_ARG;
     const size_t vb = round_up(v_elems(g) * sizeof(float), 256);
-    const bool g3 = p.g3 && workspace_bytes >= p.need3;
-    const size_t need = g3 ? p.need3 : stage_bytes(g);
+    const size_t need = stage_bytes(g);
     if (!workspace || workspace_bytes < need) return WINO_ERR_WORKSPACE;
     if (overlap(workspace, need, x, xb) || overlap(workspace, need, y, yb) || overlap(workspace, need, U, ub))
         return WINO_ERR_INVALID_ARG;
     hipStream_t s = (hipStream_t)stream;
-    if (g3) return hip_status(run_g3(x, U, y, workspace, g, (flags & WINO_FLAG_RELU) != 0, s));
+    if (p.bf3) return hip_status(launch_bf3_1d(x, U, y, workspace, g, (flags & WINO_FLAG_RELU) != 0, s));
     float* V = (float*)workspace;
     float* M = (float*)((char*)workspace + vb);
     st = hip_status(launch_input_transform(x, V, g, s));

@@ -117,6 +117,12 @@ long bf3_items(const Geom& g);               // work items: (tile blocks, filter
 bool bf3_takes(const Geom& g);               // layers and offsets the kernel handles
 double bf3_ns(const Geom& g);                // its estimated time
 hipError_t launch_bf3(const float* x, const float* U, float* y, void* ws, const Geom& g, bool relu, hipStream_t s);
+// 1-D layers in one kernel on the bf16 matrix cores, after the filters' split
+// into the workspace (us_bytes).
+long bf3_1d_items(const Geom& g);            // work items: (tile blocks, filter group)
+bool bf3_1d_takes(const Geom& g);            // layers and offsets the kernel handles
+double bf3_1d_ns(const Geom& g);             // its estimated time
+hipError_t launch_bf3_1d(const float* x, const float* U, float* y, void* ws, const Geom& g, bool relu, hipStream_t s);
 // The stages of large layers on the bf16 matrix cores, U and V as split operand
 // words (us_bytes, v3_bytes) and M in fp32.
 size_t us_bytes(const Geom& g);

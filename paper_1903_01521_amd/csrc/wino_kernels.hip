@@ -2376,14 +2376,14 @@ __global__ __launch_bounds__(256) void k_filter1d(const float* __restrict__ gw, 
 // One wave per (16-tile block, 4-channel quad), XCD-contiguous runs as in
 // k_input; lane = (tile p%16, channel c%4) loads its 8 inputs along the axis
 // (zero outside the image, past C and past P) and writes B^T d.
-template <int MT, int AX, bool V3 = false>
+template <int MT, int AX>
 __global__ __launch_bounds__(256) void k_input1d(const float* __restrict__ x, float* __restrict__ V, Geom g,
-                                                 long nwg, int nq) {
+                                                 long nwg) {
     const int lane = threadIdx.x & 63;
     const long per = (nwg + 7) / 8, item = (long)(blockIdx.x % 8) * per + blockIdx.x / 8;
     if (item >= nwg) return;
     const long w = item * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (w >= (long)g.PB * nq) return;
+    if (w >= (long)g.PB * g.CQ) return;
     const int cq = (int)(w / g.PB), pb = (int)(w % g.PB);
     const TileCoord tc = decode_tile(pb * 16 + (lane & 15), g);
     const int c = cq * 4 + (lane >> 4);
@@ -2405,8 +2405,7 @@ __global__ __launch_bounds__(256) void k_input1d(const float* __restrict__ x, fl
     }
     float v[8];
     bt8(d, v);
-    if constexpr (V3) store_v3<8>((char*)V + ((size_t)pb * (nq >> 2) + (cq >> 2)) * 8 * kUsBytes, cq & 3, lane, v);
-    else store_t4<8, true>(V + ((size_t)pb * g.CQ + cq) * 8 * 64, lane, v);
+    store_t4<8, true>(V + ((size_t)pb * g.CQ + cq) * 8 * 64, lane, v);
 }
 
 // One wave per (16-tile block, 16-filter block): lane = (tile p%16, filter
@@ -2459,14 +2458,12 @@ hipError_t launch_filter_transform_1d(const float* gw, float* U, int C, int K, i
     return hipGetLastError();
 }
 
-template <bool V3>
 static hipError_t launch_input_1d(const float* x, float* V, const Geom& g, hipStream_t s) {
-    const int nq = V3 ? (g.CQ + 3) / 4 * 4 : g.CQ;
-    const long waves = (long)g.PB * nq, nwg = (waves + 3) / 4;
+    const long waves = (long)g.PB * g.CQ, nwg = (waves + 3) / 4;
     if ((nwg + 7) / 8 * 8 > 0x7fffffffL) return hipErrorInvalidConfiguration;
     const dim3 grid((unsigned)((nwg + 7) / 8 * 8)), block(256);
 #define WINO_IN1D(MT, AX) \
-    if (g.m == MT && g.axis == AX) { hipLaunchKernelGGL((k_input1d<MT, AX, V3>), grid, block, 0, s, x, V, g, nwg, nq); return hipGetLastError(); }
+    if (g.m == MT && g.axis == AX) { hipLaunchKernelGGL((k_input1d<MT, AX>), grid, block, 0, s, x, V, g, nwg); return hipGetLastError(); }
     WINO_IN1D(6, 1) WINO_IN1D(4, 1) WINO_IN1D(2, 1) WINO_IN1D(6, 2) WINO_IN1D(4, 2) WINO_IN1D(2, 2)
 #undef WINO_IN1D
     return hipErrorInvalidValue;
@@ -2617,7 +2614,7 @@ static hipError_t launch_input_nhwc(const float* x, float* V, const Geom& g, int
 template <bool V3>
 static hipError_t input_transform(const float* x, float* V, const Geom& g, hipStream_t s) {
     const int nq = V3 ? (g.CQ + 3) / 4 * 4 : g.CQ;
-    if (g.axis != 0) return launch_input_1d<V3>(x, V, g, s);
+    if (g.axis != 0) return V3 ? hipErrorInvalidValue : launch_input_1d(x, V, g, s);
     if (g.nhwc) return launch_input_nhwc<V3>(x, V, g, nq, s);
     const long waves = (long)g.PB * nq, nwg = (waves + 3) / 4;
     if ((nwg + 7) / 8 * 8 > 0x7fffffffL) return hipErrorInvalidConfiguration;

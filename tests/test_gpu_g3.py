@@ -3,8 +3,7 @@ filters and the transformed input stored as three bf16 terms), against the fp64
 direct oracle at the edges of the kernel's tiles: filters, tiles and channels
 that leave remainders in the 128-filter, 128-tile and 16-channel blocks, step
 counts of every residue of the kernel's unrolled loop, NCHW and channel-last
-tensors (by tile rows, and by region for other channel counts and widths), and
-1-D filters along either axis.
+tensors (by tile rows, and by region for other channel counts and widths).
 
 A layer runs this path when AUTO asks for exactly its workspace.  Tolerances:
 the gates of the fp32 paths."""
@@ -71,30 +70,6 @@ def test_g3_edges(shape):
         out = h.host(y)
         out = out.reshape(N, H, W, K).transpose(0, 3, 1, 2) if nhwc else out.reshape(N, K, H, W)
         _check(out, ref, TOL[m])
-
-
-# (N, C, H, W, K, m, r, axis): steps 27 and 31
-@pytest.mark.parametrize("shape", [(40, 420, 28, 28, 500, 6, 3, "w"), (30, 491, 25, 29, 500, 4, 5, "h")],
-                         ids=lambda s: "x".join(map(str, s)))
-def test_g3_1d(shape):
-    N, C, H, W, K, m, r, axis = shape
-    print(f"g3 1-D shape={shape}", flush=True)
-    pad = r // 2
-    R, S = (1, r) if axis == "w" else (r, 1)
-    x, g = _inputs(N, C, H, W, K, R, S, N + C)
-    pads = ((0, 0), (0, 0), (0, 0), (pad, pad)) if axis == "w" else ((0, 0), (0, 0), (pad, pad), (0, 0))
-    ref = direct.conv2d(np.pad(x, pads), g, 0)
-    P = N * (H * -(-W // m) if axis == "w" else -(-H // m) * W)
-    ax = B.WINO_AXIS_W if axis == "w" else B.WINO_AXIS_H
-    U = h.empty_bytes(B.wino_filter_bytes_1d(C, K, m, r))
-    B.check(B.wino_filter_transform_1d(h.dev(g.reshape(K, C, r)), U, C, K, m, r))
-    wsb = B.wino_workspace_bytes_1d(N, C, H, W, K, pad, m, r, ax, 0)
-    assert wsb == workspace(8, P, C, K), "the layer runs on the bf16 matrix cores"
-    ws, y = h.empty_bytes(wsb), h.empty_bytes(4 * N * K * H * W)
-    ws.fill_(float("nan"))
-    y.fill_(float("nan"))
-    B.check(B.wino_conv2d_1d(h.dev(x), U, y, N, C, H, W, K, pad, m, r, ax, 0, ws, wsb))
-    _check(h.host(y).reshape(N, K, H, W), ref, 1e-3)
 
 
 def test_g3_without_its_workspace():
