@@ -285,8 +285,11 @@ void choose_g3(const Geom& g, unsigned flags, Plan* p) {
 // 16-channel step where few workgroups run.  With few tiles and many channels
 // they win (N = 1 192-channel 17x17: 22 against 30 us), as the one kernel's steps
 // take 2 us each; else the one kernel (N = 3 33 -> 50 at 101x37: 22 -> 15 us).
+// Not below 12 channels: what the split drops is then as large as the fp32
+// sums' rounding (8 channels, 1x5: 3.54e-7 against 3.46e-7 from the exact
+// result, 5 channels, 1x3: 3.6e-7 against 3.3e-7; 12, 1x7: 4.2e-7 against 4.4e-7).
 bool choose_bf3_1d(const Geom& g, const Plan& p) {
-    if (!p.automatic || g.axis == 0 || !bf3_1d_takes(g) || us_bytes(g) > stage_bytes(g)) return false;
+    if (!p.automatic || g.axis == 0 || g.C < 12 || !bf3_1d_takes(g) || us_bytes(g) > stage_bytes(g)) return false;
     const double x = 4.0 * g.N * g.C * g.H * g.W, y = 4.0 * g.N * g.K * g.Ho * g.Wo;
     const double gemm = 2.0 * g.T * g.P * (double)g.C * g.K / 105000.0, chain = 800.0 * ((g.CQ + 3) / 4);
     const double stages = 14500.0 + (x + 4.0 * v_elems(g)) / 4800.0 + (4.0 * m_elems(g) + y) / 5600.0 +

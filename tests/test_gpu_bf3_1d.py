@@ -23,7 +23,7 @@ SHAPES = [
     (2, 20, 57, 58, 130, 0, 4, 5),      # no padding, two filter groups, the last with one block
     (2, 17, 9, 20, 40, 9, 6, 3),        # regions wholly outside the image
     (2, 17, 9, 1, 16, 7, 2, 7),         # one column: regions that begin rows before the tensor
-    (5, 5, 7, 3, 7, 2, 4, 5),           # images smaller than a tile row
+    (5, 13, 7, 3, 7, 2, 4, 5),          # images smaller than a tile row
     (64, 48, 28, 29, 272, 1, 6, 3),     # three filter groups, several rounds of workgroups
     (40, 420, 28, 28, 500, 1, 6, 3),    # 27 steps
     (30, 491, 25, 29, 500, 2, 4, 5),    # 31 steps
