@@ -136,8 +136,10 @@ extern "C" {
  * significand bits, the whole fp32 exponent range) and the six largest of the
  * nine products are summed in fp32, for 2.67 times the fp32 matrix rate.  The
  * dropped products are below 2^-21 of |u v|; errors against 64 bits are no
- * larger than the fp32 kernels'.  An infinite or NaN input gives NaN wherever
- * those give an infinity or NaN.  The filters' split goes to the workspace
+ * larger than the fp32 kernels'.  Infinite and NaN
+ * inputs (and sums that overflow) give what those kernels give, also with
+ * WINO_FLAG_RELU: the 16-tile x 16-filter blocks with a result that is not finite
+ * are computed once more on fp32 MFMA.  The filters' split goes to the workspace
  * (6 bytes per element of U, with the channels in whole steps of 16) in every
  * call; without that workspace AUTO runs the kernels below.  An explicitly
  * chosen algorithm always runs on fp32 MFMA. */

@@ -192,7 +192,7 @@ hipError_t run_g3(const float* x, const float* U, float* y, void* ws, const Geom
     float* M = (float*)(V + round_up(v3_bytes(g), 256));
     hipError_t e = launch_usplit(U, ws, g, s);
     if (e == hipSuccess) e = launch_input_transform3(x, V, g, s);
-    if (e == hipSuccess) e = launch_gemm3(ws, V, M, g, s);
+    if (e == hipSuccess) e = launch_gemm3(ws, V, x, U, M, g, s);
     if (e == hipSuccess) e = launch_output_transform(M, y, g, relu, s);
     return e;
 }

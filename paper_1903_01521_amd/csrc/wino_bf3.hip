@@ -126,7 +126,7 @@ __device__ __forceinline__ void bf3_bt(const float (&a)[6], float (&r)[6]) {
 
 template <int MT, int R, bool RAG>
 __global__ __launch_bounds__(512) void k_bf3(const float* __restrict__ x, const char* __restrict__ US,
-                                             float* __restrict__ y, Geom g, FusedTiling ft, int relu, int vec_ok,
+                                             const float* __restrict__ U, float* __restrict__ y, Geom g, FusedTiling ft, int relu, int vec_ok,
                                              int nts) {
     using S = Bf3Shape<MT, R>;
     constexpr int A = S::A, T = S::T, HN = S::HN, NP = S::NP, FB = S::FB, TB = S::TB, D = S::D, UN = S::UN, PAD = S::PAD;
@@ -373,6 +373,7 @@ __global__ __launch_bounds__(512) void k_bf3(const float* __restrict__ x, const 
 #pragma unroll
     for (int c = 0; c < OWN; ++c) ot[c] = decode_tile((tp * TB + (wp * OWN + c) % TB) * 16 + (lane & 15), g);
     float* const ex = (float*)vs;
+    float chk[OWN] = {};                           // NaN once an output of the block is not finite
     auto slot = [&](int owner, int idx, int c, int rr) -> float* {
         return ex + (((((wf * 4 + owner) * 3 + idx) * OWN + c) * RS + rr) * NO) * 64;
     };
@@ -429,10 +430,32 @@ __global__ __launch_bounds__(512) void k_bf3(const float* __restrict__ x, const 
 #pragma unroll
                     for (int e = 0; e < 4; ++e) o[(4 * k + e) / MT][(4 * k + e) % MT] = q[e];
                 }
+#pragma unroll
+                for (int i = 0; i < NO; ++i) chk[c] = __builtin_fmaf(o[i / MT][i % MT], 0.0f, chk[c]);
                 const int k = (kgi * S::KGW + wf * FB + (wp * OWN + c) / TB) * 16 + 4 * cl + r0 + rr;
                 if (nts) store_block<MT, true>(y, g, ot[c], k, o, rl, vo);
                 else store_block<MT, false>(y, g, ot[c], k, o, rl, vo);
             }
+    }
+    // An operand that is infinite or NaN has no split: every result it enters is
+    // NaN here.  Such blocks (and those whose sums overflow) run once more on
+    // fp32 MFMA, which gives the infinities and NaNs of the other kernels.
+#pragma unroll 1
+    for (int c = 0; c < OWN; ++c) {
+        const int b = wp * OWN + c, kb = kgi * S::KGW + wf * FB + b / TB;
+        if (kb >= g.KB || !__any(OWN == 1 || c == 0 ? chk[0] != chk[0] : chk[OWN - 1] != chk[OWN - 1])) continue;
+        const int q0 = (tp * TB + b % TB) * 16;
+        const TileCoord qt = decode_tile(q0 + (lane & 15), g);
+        f32x4 m[T];
+        fp32_products<MT, R>(x, U, g, q0, kb, lane, m);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            float m1[T], o[MT][MT];
+#pragma unroll
+            for (int t = 0; t < T; ++t) m1[t] = m[t][r];
+            output_tf<MT, R>(m1, o);
+            store_block<MT, false>(y, g, qt, kb * 16 + 4 * cl + r, o, rl, vo);
+        }
     }
 }
 
@@ -491,10 +514,10 @@ static hipError_t bf3_instance(const float* x, const float* U, float* y, void* w
     const dim3 grid((unsigned)(8 * ft.per)), block(512);
     const int vec_ok = (g.Wo % MT == 0) && aligned(y, 4 * MT);
     if (g.W % MT == 0)
-        hipLaunchKernelGGL((k_bf3<MT, R, false>), grid, block, 0, s, x, (const char*)ws, y, g, ft, (int)relu, vec_ok,
+        hipLaunchKernelGGL((k_bf3<MT, R, false>), grid, block, 0, s, x, (const char*)ws, U, y, g, ft, (int)relu, vec_ok,
                            split_stream_stores(g));
     else
-        hipLaunchKernelGGL((k_bf3<MT, R, true>), grid, block, 0, s, x, (const char*)ws, y, g, ft, (int)relu, vec_ok,
+        hipLaunchKernelGGL((k_bf3<MT, R, true>), grid, block, 0, s, x, (const char*)ws, U, y, g, ft, (int)relu, vec_ok,
                            split_stream_stores(g));
     return hipGetLastError();
 }

@@ -27,8 +27,8 @@ constexpr int kL1FB = 2, kL1TB = 2, kL1Waves = 4;
 
 template <int MT, int AX>
 __global__ __launch_bounds__(256, 2) void k_bf3_1d(const float* __restrict__ x, const char* __restrict__ US,
-                                                   float* __restrict__ y, Geom g, int nkg, int kgw, int items, int per,
-                                                   int relu, int vec2) {
+                                                   const float* __restrict__ U, float* __restrict__ y, Geom g, int nkg,
+                                                   int kgw, int items, int per, int relu, int vec2) {
     constexpr int T = 8, FB = kL1FB, TB = kL1TB, D = 4, UN = TB * 4 / kL1Waves;
     __shared__ uint4 vs[2 * T * TB * 128];             // [stage][t][tile block][X | Y][64 lanes]
     const int tid = threadIdx.x, lane = tid & 63;
@@ -192,41 +192,84 @@ __global__ __launch_bounds__(256, 2) void k_bf3_1d(const float* __restrict__ x, 
     }
     if (!work) return;
 
+    // Outputs of the 16 filters of block kb from their products m; true where one
+    // of them is not finite (before ReLU).
+    auto store = [&](const TileCoord& ot, int kb, const f32x4 (&m)[T]) -> bool {
+        float chk = 0.0f;                              // NaN once an output is not finite
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int k = kb * 16 + 4 * cl + r;
+            float a[8], o[MT];
+#pragma unroll
+            for (int t = 0; t < T; ++t) a[t] = m[t][r];
+            at8<MT>(a, o);
+#pragma unroll
+            for (int i = 0; i < MT; ++i) chk = __builtin_fmaf(o[i], 0.0f, chk);
+            if (!ot.valid || k >= g.K) continue;
+            float* yk = y + ((size_t)ot.n * g.K + k) * g.Ho * g.Wo;
+#pragma unroll
+            for (int i = 0; i < MT; ++i) o[i] = relu ? fmaxf(o[i], 0.0f) : o[i];
+            if constexpr (AX == 1) {
+                float* const row = yk + (size_t)ot.ti * g.Wo;
+                const int col = ot.tj * MT;
+#pragma unroll
+                for (int i = 0; i < MT; i += 2) {
+                    if (vec2 && col + i + 1 < g.Wo) {
+                        store_out<false>(row + col + i, o[i], o[i + 1]);
+                    } else {
+                        if (col + i < g.Wo) row[col + i] = o[i];
+                        if (col + i + 1 < g.Wo) row[col + i + 1] = o[i + 1];
+                    }
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < MT; ++i)
+                    if (ot.ti * MT + i < g.Ho) yk[(size_t)(ot.ti * MT + i) * g.Wo + ot.tj] = o[i];
+            }
+        }
+        return chk != chk;
+    };
+    uint32_t redo = 0;                                 // bit b * FB + f: a block to run again
 #pragma unroll
     for (int b = 0; b < TB; ++b) {
         const TileCoord ot = decode_tile((tp * TB + b) * 16 + (lane & 15), g);
-        if (!ot.valid) continue;
 #pragma unroll
         for (int f = 0; f < FB; ++f)
+            if (__any(store(ot, kbw + f, acc[f][b]))) redo |= 1u << (b * FB + f);
+    }
+    // An operand that is infinite or NaN has no split: every result it enters is
+    // NaN here.  Such blocks (and those whose sums overflow) run once more on
+    // fp32 MFMA, which gives the infinities and NaNs of the three stages.
+#pragma unroll 1
+    for (int i = 0; i < TB * FB; ++i) {
+        const int kb = kbw + i % FB;
+        if (!(redo >> i & 1) || kb >= g.KB) continue;
+        const TileCoord ot = decode_tile((tp * TB + i / FB) * 16 + (lane & 15), g);
+        f32x4 m[T];
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int k = (kbw + f) * 16 + 4 * cl + r;
-                if (k >= g.K) continue;
-                float a[8], o[MT];
+        for (int t = 0; t < T; ++t) m[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+        const int q0 = AX == 1 ? ot.ti : ot.ti * MT - g.pad, q1 = AX == 1 ? ot.tj * MT - g.pad : ot.tj;
+#pragma unroll 1
+        for (int cq = 0; cq < g.CQ; ++cq) {
+            const int c = cq * 4 + cl;
+            const float* xc = x + ((size_t)ot.n * g.C + (c < g.C ? c : 0)) * g.H * g.W;
+            float d[8], v[8];
 #pragma unroll
-                for (int t = 0; t < T; ++t) a[t] = acc[f][b][t][r];
-                at8<MT>(a, o);
-                float* yk = y + ((size_t)ot.n * g.K + k) * g.Ho * g.Wo;
-#pragma unroll
-                for (int i = 0; i < MT; ++i) o[i] = relu ? fmaxf(o[i], 0.0f) : o[i];
-                if constexpr (AX == 1) {
-                    float* const row = yk + (size_t)ot.ti * g.Wo;
-                    const int col = ot.tj * MT;
-#pragma unroll
-                    for (int i = 0; i < MT; i += 2) {
-                        if (vec2 && col + i + 1 < g.Wo) {
-                            store_out<false>(row + col + i, o[i], o[i + 1]);
-                        } else {
-                            if (col + i < g.Wo) row[col + i] = o[i];
-                            if (col + i + 1 < g.Wo) row[col + i + 1] = o[i + 1];
-                        }
-                    }
-                } else {
-#pragma unroll
-                    for (int i = 0; i < MT; ++i)
-                        if (ot.ti * MT + i < g.Ho) yk[(size_t)(ot.ti * MT + i) * g.Wo + ot.tj] = o[i];
-                }
+            for (int u = 0; u < 8; ++u) {
+                const int row = AX == 1 ? q0 : q0 + u, col = AX == 1 ? q1 + u : q1;
+                d[u] = ot.valid && c < g.C && (unsigned)row < (unsigned)g.H && (unsigned)col < (unsigned)g.W
+                           ? xc[(size_t)row * g.W + col] : 0.0f;
             }
+            bt8(d, v);
+            const float* ug = U + ((size_t)kb * g.CQ + cq) * T * 64 + lane * 4;
+#pragma unroll
+            for (int g4 = 0; g4 < T / 4; ++g4) {
+                const f32x4 u = *(const f32x4*)(ug + g4 * 256);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) m[4 * g4 + e] = mfma16x16x4(u[e], v[4 * g4 + e], m[4 * g4 + e]);
+            }
+        }
+        store(ot, kb, m);
     }
 }
 
@@ -256,7 +299,7 @@ hipError_t launch_bf3_1d(const float* x, const float* U, float* y, void* ws, con
     const dim3 grid((unsigned)(8 * per)), block(256);
 #define WINO_L1(MT, AX) \
     if (g.m == MT && g.axis == AX) { \
-        hipLaunchKernelGGL((k_bf3_1d<MT, AX>), grid, block, 0, s, x, (const char*)ws, y, g, nkg, kgw, items, per, (int)relu, vec2); \
+        hipLaunchKernelGGL((k_bf3_1d<MT, AX>), grid, block, 0, s, x, (const char*)ws, U, y, g, nkg, kgw, items, per, (int)relu, vec2); \
         return hipGetLastError(); \
     }
     WINO_L1(6, 1) WINO_L1(4, 1) WINO_L1(2, 1) WINO_L1(6, 2) WINO_L1(4, 2) WINO_L1(2, 2)

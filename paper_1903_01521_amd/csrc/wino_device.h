@@ -195,6 +195,35 @@ __device__ __forceinline__ void load_region(const RegionPlan<MT, A>& rp, const G
     }
 }
 
+// Products of one (16-tile block at tile p0, filter block kb) at all T positions
+// on fp32 MFMA, straight from x and U: what the kernels that split their
+// operands in three run again where a result is not finite.  A lane gets the
+// accumulator words of M (tile lane % 16, filters 4 * (lane / 16) .. +3).
+template <int MT, int R>
+__device__ __forceinline__ void fp32_products(const float* __restrict__ x, const float* __restrict__ U, const Geom& g,
+                                              int p0, int kb, int lane, f32x4 (&acc)[(MT + R - 1) * (MT + R - 1)]) {
+    constexpr int A = MT + R - 1, T = A * A;
+    const int cl = lane >> 4;
+    const TileCoord tc = decode_tile(p0 + (lane & 15), g);
+    const RegionPlan<MT, A> rp = make_region_plan<MT, A>(x, g, p0, tc, cl);
+    const __amdgpu_buffer_rsrc_t ur = u_rsrc(U, g);
+#pragma unroll
+    for (int t = 0; t < T; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+    for (int cq = 0; cq < g.CQ; ++cq) {
+        float d[A][A], v[T];
+        load_region<MT, A>(rp, g, cq, cl, d);
+        input_tf<A - 2>(d, v);
+        const uint32_t grp = __builtin_amdgcn_readfirstlane((uint32_t)(kb * g.CQ + cq) * (T / 4) * 1024u);
+#pragma unroll
+        for (int g4 = 0; g4 < T / 4; ++g4) {
+            const f32x4 u = u_load(ur, (uint32_t)lane * 16u, grp + g4 * 1024u);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[4 * g4 + e] = mfma16x16x4(u[e], v[4 * g4 + e], acc[4 * g4 + e]);
+        }
+    }
+}
+
 // Output rows leave through streaming (non-temporal) stores where a kernel
 // writes whole cache lines: y is not read back, so it need not displace cached
 // inputs.  Where the lines of a row are completed by several store

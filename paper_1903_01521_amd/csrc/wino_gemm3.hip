@@ -18,7 +18,56 @@ namespace wino {
 // much as the products (step of this size 4800 cycles, 2200 of them products).
 constexpr int kG3K = 8, kG3P = 8;                      // filter and tile blocks of a workgroup
 
+// B^T of 4 and of 6 points by rows.
+__device__ const float kBt4[4][4] = {{1, 0, -1, 0}, {0, 1, 1, 0}, {0, -1, 1, 0}, {0, 1, 0, -1}};
+__device__ const float kBt6[6][6] = {{4, 0, -5, 0, 1, 0}, {0, -4, -4, 1, 1, 0}, {0, 4, -4, -1, 1, 0},
+                                     {0, -2, -1, 2, 1, 0}, {0, 2, -1, -2, 1, 0}, {0, 4, 0, -5, 0, 1}};
+
+// M of (tile block pb, filter blocks kb .. kb+FB-1) at position t on fp32 MFMA,
+// straight from x and U.  Only the region elements that B^T weighs are read: a
+// zero times an infinity would be NaN.
+template <int FB>
+__device__ __forceinline__ void fp32_position(const float* __restrict__ x, const float* __restrict__ U, const Geom& g,
+                                              int pb, int kb, int t, int lane, float* __restrict__ M) {
+    const int A = g.A, xi = t / A, nu = t % A, cl = lane >> 4;
+    const float* const bx = A == 4 ? kBt4[xi] : kBt6[xi];
+    const float* const bn = A == 4 ? kBt4[nu] : kBt6[nu];
+    const TileCoord tc = decode_tile(pb * 16 + (lane & 15), g);
+    const int r0 = tc.ti * g.m - g.pad, c0 = tc.tj * g.m - g.pad;
+    const size_t chan = g.nhwc ? 1 : (size_t)g.H * g.W, pix = g.nhwc ? g.C : 1;
+    f32x4 acc[FB];
+#pragma unroll
+    for (int f = 0; f < FB; ++f) acc[f] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+    for (int cq = 0; cq < g.CQ; ++cq) {
+        const int c = cq * 4 + cl;
+        const bool ok = tc.valid && c < g.C;
+        const float* const xc = x + (size_t)tc.n * g.C * g.H * g.W + (ok ? c : 0) * chan;
+        float v = 0.0f;
+        for (int i = 0; i < A; ++i) {
+            if (bx[i] == 0.0f) continue;
+            float s = 0.0f;
+            for (int j = 0; j < A; ++j) {
+                if (bn[j] == 0.0f) continue;
+                const int row = r0 + i, col = c0 + j;
+                const bool in = ok && (unsigned)row < (unsigned)g.H && (unsigned)col < (unsigned)g.W;
+                s = __builtin_fmaf(bn[j], in ? xc[((size_t)row * g.W + col) * pix] : 0.0f, s);
+            }
+            v = __builtin_fmaf(bx[i], s, v);
+        }
+#pragma unroll
+        for (int f = 0; f < FB; ++f) {
+            const size_t k = min(kb + f, g.KB - 1);
+            acc[f] = mfma16x16x4(U[(((k * g.CQ + cq) * (g.T / 4) + t / 4) * 64 + lane) * 4 + t % 4], v, acc[f]);
+        }
+    }
+#pragma unroll
+    for (int f = 0; f < FB; ++f)
+        if (kb + f < g.KB) *(f32x4*)(M + (((size_t)pb * g.KB + kb + f) * g.T + t) * 256 + lane * 4) = acc[f];
+}
+
 __global__ __launch_bounds__(512) void k_gemm3(const char* __restrict__ US, const char* __restrict__ V3,
+                                               const float* __restrict__ x, const float* __restrict__ U,
                                                float* __restrict__ M, Geom g) {
     constexpr int FB = kG3K / 2, PB = kG3P, BLK = 4 * kUsBytes;   // BLK: a tile block's four positions
     __shared__ uint4 st0[PB * BLK / 16], st1[PB * BLK / 16], st2[PB * BLK / 16];
@@ -131,12 +180,28 @@ __global__ __launch_bounds__(512) void k_gemm3(const char* __restrict__ US, cons
         if (s + 5 < nsteps) step(IC<5>{}, s + 5);
     }
     __builtin_amdgcn_s_waitcnt(0);                     // no load outlives the loop
+    uint32_t redo = 0;                                 // bit b: a product of tile block b is not finite
 #pragma unroll
-    for (int b = 0; b < PB; ++b)
+    for (int b = 0; b < PB; ++b) {
+        float chk = 0.0f;                              // NaN once a product is not finite
 #pragma unroll
-        for (int f = 0; f < FB; ++f)
+        for (int f = 0; f < FB; ++f) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) chk = __builtin_fmaf(acc[f][b][r], 0.0f, chk);
             if (kbw + f < g.KB && pb0 + b < g.PB)
                 *(f32x4*)(M + (((size_t)(pb0 + b) * g.KB + kbw + f) * T + tg * 4 + we) * 256 + lane * 4) = acc[f][b];
+        }
+        if (__any(chk != chk)) redo |= 1u << b;
+    }
+    // An operand that is infinite or NaN has no split: every product it enters is
+    // NaN here.  Such tile blocks (and those whose sums overflow) run once more
+    // on fp32 MFMA, straight from x and U, which gives the other kernels'
+    // infinities and NaNs.
+#pragma unroll 1
+    for (; redo; redo &= redo - 1) {
+        const int pb = pb0 + __builtin_ctz(redo);
+        if (pb < g.PB) fp32_position<FB>(x, U, g, pb, kbw, tg * 4 + we, lane, M);
+    }
 }
 
 // Bytes of the split filters and of the split transformed input: the layer's K,
@@ -153,10 +218,11 @@ long gemm3_items(const Geom& g) {
     return (long)(g.T / 4) * ((g.PB + kG3P - 1) / kG3P) * ((g.KB + kG3K - 1) / kG3K);
 }
 
-hipError_t launch_gemm3(const void* US, const void* V3, float* M, const Geom& g, hipStream_t s) {
+hipError_t launch_gemm3(const void* US, const void* V3, const float* x, const float* U, float* M, const Geom& g,
+                        hipStream_t s) {
     const long wgs = (gemm3_items(g) + 7) / 8 * 8;
     if (wgs > 0x7fffffffL) return hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL(k_gemm3, dim3((unsigned)wgs), dim3(512), 0, s, (const char*)US, (const char*)V3, M, g);
+    hipLaunchKernelGGL(k_gemm3, dim3((unsigned)wgs), dim3(512), 0, s, (const char*)US, (const char*)V3, x, U, M, g);
     return hipGetLastError();
 }
 

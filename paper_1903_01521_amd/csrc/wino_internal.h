@@ -131,7 +131,9 @@ hipError_t launch_usplit(const float* U, void* US, const Geom& g, hipStream_t s)
 hipError_t launch_input_transform3(const float* x, void* V3, const Geom& g, hipStream_t s);
 bool gemm3_takes(const Geom& g);
 long gemm3_items(const Geom& g);
-hipError_t launch_gemm3(const void* US, const void* V3, float* M, const Geom& g, hipStream_t s);
+// x and U: where M is not finite it is computed once more from them in fp32.
+hipError_t launch_gemm3(const void* US, const void* V3, const float* x, const float* U, float* M, const Geom& g,
+                        hipStream_t s);
 // Low-C path (C <= 4): a lane per tile, vector FMAs over the few channels.
 hipError_t launch_lowc(const float* x, const float* U, float* y, const Geom& g, bool relu, hipStream_t s);
 hipError_t launch_maxpool2x2(const float* x, float* y, int N, int C, int H, int W, hipStream_t s);
