@@ -133,11 +133,12 @@ extern "C" {
 
 /* WINO_ALGO_AUTO runs large fp32 "same" layers (pad (r-1)/2, NCHW), deep ones
  * (also channel-last) and most 1-D ones on the bf16 matrix cores: U and V are split exactly into three bf16 terms each (24
- * significand bits, the whole fp32 exponent range) and the six largest of the
+ * significand bits; scaled by 2^16, so that every fp32 value below 2^112 has
+ * its split, down to the smallest) and the six largest of the
  * nine products are summed in fp32, for 2.67 times the fp32 matrix rate.  The
  * dropped products are below 2^-21 of |u v|; errors against 64 bits are no
  * larger than the fp32 kernels'.  Infinite and NaN
- * inputs (and sums that overflow) give what those kernels give, also with
+ * inputs (and sums that overflow, here from 2^96) give what those kernels give, also with
  * WINO_FLAG_RELU: the 16-tile x 16-filter blocks with a result that is not finite
  * are computed once more on fp32 MFMA.  The filters' split goes to the workspace
  * (6 bytes per element of U, with the channels in whole steps of 16) in every

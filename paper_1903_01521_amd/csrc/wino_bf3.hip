@@ -3,8 +3,7 @@
 //
 // v_mfma_f32_16x16x4_f32 runs at 1/16 of the rate of v_mfma_f32_16x16x32_bf16.
 // A fp32 value's 24 significand bits are exactly h + m + l, three bf16 values
-// of 8 bits each (h and m cut off or rounded, l what is left), over the whole
-// fp32 exponent range.  u*v is then the sum of nine products, of which
+// of 8 bits each (h and m cut off or rounded, l what is left).  u*v is then the sum of nine products, of which
 // the six largest,
 //     hh + hm + mh + hl + mm + lh,
 // leave an error below 2^-21 |u v| (the dropped ml + lm + ll; about 2^-24 on
@@ -62,7 +61,7 @@ __global__ __launch_bounds__(256) void k_usplit(const float* __restrict__ U, cha
     for (int e = 0; e < 4; ++e) {
         uint32_t X[4], Y[4];
 #pragma unroll
-        for (int d = 0; d < 4; ++d) split3_rounded(u[d][e], X[d], Y[d]);
+        for (int d = 0; d < 4; ++d) split3_rounded(u[d][e] * kSplitScale, X[d], Y[d]);
         char* o = US + ((kc * TG + tg) * 4 + e) * kUsBytes;
         *(uint4*)(o + lane * 16) = make_uint4(X[0], X[1], X[2], X[3]);
         *(uint2*)(o + 1024 + lane * 8) = make_uint2(__builtin_amdgcn_perm(Y[1], Y[0], 0x07060302u),
@@ -75,7 +74,7 @@ __global__ __launch_bounds__(256) void k_usplit(const float* __restrict__ U, cha
 // registers per lane) owns 64 filters x 32 consecutive tiles (alpha = 6) or 64
 // tiles (alpha = 4) at all T positions.  Per 16 channels:
 //   - each wave transforms the regions of 16 tiles x 4 channels (x to registers,
-//     loaded during the previous step's products), splits the T values and
+//     loaded after the previous step's products), splits the T values and
 //     writes them to LDS as MFMA operands (147 KB: one stage, so transforms and
 //     products alternate between two barriers);
 //   - wave (position quarter wp, filter half wf) multiplies 32 filters x all
@@ -89,8 +88,8 @@ __global__ __launch_bounds__(256) void k_usplit(const float* __restrict__ U, cha
 // before the first step and 13000 of epilogue.  What that measured on the way
 // there (this layer): 8-byte filter elements (X and Y) 650 us, 6-byte ones 595,
 // the outer region columns from the neighbouring lanes instead of by loads of
-// their own 540; loads one at a time between the products instead of four at
-// once held no wave at issue but changed nothing by itself.
+// their own 540.  2^16 in B^T and 2^-32 and the check in the epilogue cost 1-2%
+// (582 -> 590, N = 32 64-channel 224x224 354 -> 363).
 // Against fp32 MFMA kernels: N = 32 64-channel 224x224 532 -> 352 us, N = 32
 // 128-channel 112x112 427 -> 293, N = 32 512-channel 14x14 F(2x2) 143 -> 128,
 // N = 64 256-channel 56x56 616 -> 578, N = 32 5x5 48 -> 64 at 35x35 50 -> 40.
@@ -111,17 +110,33 @@ struct Bf3Shape {
     static_assert(NP % D == 0, "the ring wraps onto the next step's slots");
 };
 
-// B^T of 4 and of 6 points, 12 operations for the latter.
-__device__ __forceinline__ void bf3_bt(const float (&a)[4], float (&r)[4]) { bt_1d(a, r); }
+// B^T of 4 and of 6 points, 12 operations for the latter; SC: times kSplitScale
+// (powers of two, so the rounding is the same), 2 or 3 operations more.
+template <bool SC>
+__device__ __forceinline__ void bf3_bt(const float (&a)[4], float (&r)[4]) {
+    if constexpr (SC) {
+        constexpr float S = kSplitScale;
+        const float s1 = S * a[1], s2 = S * a[2];
+        r[0] = __builtin_fmaf(S, a[0], -s2);
+        r[1] = s1 + s2;
+        r[2] = s2 - s1;
+        r[3] = __builtin_fmaf(-S, a[3], s1);
+    } else {
+        bt_1d(a, r);
+    }
+}
+template <bool SC>
 __device__ __forceinline__ void bf3_bt(const float (&a)[6], float (&r)[6]) {
-    const float d31 = a[3] - a[1], d42 = a[4] - a[2];
-    const float p = __builtin_fmaf(-4.0f, a[2], a[4]), q = __builtin_fmaf(-4.0f, a[1], a[3]);
-    r[0] = __builtin_fmaf(4.0f, a[0], __builtin_fmaf(-5.0f, a[2], a[4]));    //  4a0 - 5a2 + a4
-    r[1] = p + q;                                                            // -4a1 - 4a2 + a3 + a4
-    r[2] = p - q;                                                            //  4a1 - 4a2 - a3 + a4
-    r[3] = __builtin_fmaf(2.0f, d31, d42);                                   // -2a1 - a2 + 2a3 + a4
-    r[4] = __builtin_fmaf(-2.0f, d31, d42);                                  //  2a1 - a2 - 2a3 + a4
-    r[5] = __builtin_fmaf(4.0f, a[1], __builtin_fmaf(-5.0f, a[3], a[5]));    //  4a1 - 5a3 + a5
+    constexpr float S = SC ? kSplitScale : 1.0f;
+    const float s3 = S * a[3], s4 = S * a[4], s5 = S * a[5];
+    const float d31 = __builtin_fmaf(-S, a[1], s3), d42 = __builtin_fmaf(-S, a[2], s4);
+    const float p = __builtin_fmaf(-4.0f * S, a[2], s4), q = __builtin_fmaf(-4.0f * S, a[1], s3);
+    r[0] = __builtin_fmaf(4.0f * S, a[0], __builtin_fmaf(-5.0f * S, a[2], s4));    //  4a0 - 5a2 + a4
+    r[1] = p + q;                                                                  // -4a1 - 4a2 + a3 + a4
+    r[2] = p - q;                                                                  //  4a1 - 4a2 - a3 + a4
+    r[3] = __builtin_fmaf(2.0f, d31, d42);                                         // -2a1 - a2 + 2a3 + a4
+    r[4] = __builtin_fmaf(-2.0f, d31, d42);                                        //  2a1 - a2 - 2a3 + a4
+    r[5] = __builtin_fmaf(4.0f * S, a[1], __builtin_fmaf(-5.0f * S, a[3], s5));    //  4a1 - 5a3 + a5
 }
 
 template <int MT, int R, bool RAG>
@@ -239,7 +254,7 @@ __global__ __launch_bounds__(512) void k_bf3(const float* __restrict__ x, const 
             float c[A], r[A];
 #pragma unroll
             for (int u = 0; u < A; ++u) c[u] = d[u][v];
-            bf3_bt(c, r);
+            bf3_bt<true>(c, r);
 #pragma unroll
             for (int u = 0; u < A; ++u) t1[u][v] = r[u];
         }
@@ -247,7 +262,7 @@ __global__ __launch_bounds__(512) void k_bf3(const float* __restrict__ x, const 
 #pragma unroll
         for (int u = 0; u < A; ++u) {
             float r[A];
-            bf3_bt(t1[u], r);
+            bf3_bt<false>(t1[u], r);
 #pragma unroll
             for (int v = 0; v < A; ++v) {
                 uint32_t X, Y;
@@ -322,16 +337,14 @@ __global__ __launch_bounds__(512) void k_bf3(const float* __restrict__ x, const 
             vY[i & 1] = vsrc[(pt * TB + i % TB) * 128 + 64];
         };
         uint4 uY[FB];
-        // Global loads go out one at a time between the products (four at once
-        // held a wave at issue for 250-480 cycles): in position p the filters
-        // that take position p-1's place in the ring, and a share of the next
-        // step's regions (past the last step every lane's offset is invalid).
+        // The filters that take position p-1's place in the ring load one at a time
+        // between the products of position p (four at once held a wave at issue
+        // for 250-480 cycles).
         auto slot = [&](auto pc, auto kc) {
-            constexpr int p = decltype(pc)::value, k = decltype(kc)::value, NS = 3 * TB, i = p * NS + k;
+            constexpr int p = decltype(pc)::value, k = decltype(kc)::value, NS = 3 * TB;
             __builtin_amdgcn_sched_barrier(0);
             if constexpr (p >= 1 && p - 1 + D < NP && k * 2 * FB / NS < (k + 1) * 2 * FB / NS)
                 load_u1(s, IC<p - 1 + D>{}, IC<k * 2 * FB / NS>{});
-            static_for<i * NX / (NP * NS), (i + 1) * NX / (NP * NS)>([&](auto nc) { load_x(s + 1, nc); });
             __builtin_amdgcn_sched_barrier(0);
         };
         load_v(IC<0>{});
@@ -356,8 +369,13 @@ __global__ __launch_bounds__(512) void k_bf3(const float* __restrict__ x, const 
             slot(IC<p>{}, IC<3 * b + 2>{});
         });
         if (more) {
+            // Not between the products: loads return in order, so the filters' waits
+            // would wait for x from HBM too (N = 64 256-channel 56x56 layer 705
+            // against 596 us).
+            static_for<0, NX>([&](auto nc) { load_x(s + 1, nc); });
             wait_vm_lds<63>();
             wg_barrier();                          // every wave is done with this step's V
+            __builtin_amdgcn_sched_barrier(0);
             transform_all(s + 1);
             wait_vm_lds<63>();
             wg_barrier();                          // the next step's V is written
@@ -428,7 +446,7 @@ __global__ __launch_bounds__(512) void k_bf3(const float* __restrict__ x, const 
 #pragma unroll
                     for (int i = 0; i < 3; ++i) q += *(const f32x4*)(slot(wp, i, c, rr) + lane * 4 + k * 256);
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) o[(4 * k + e) / MT][(4 * k + e) % MT] = q[e];
+                    for (int e = 0; e < 4; ++e) o[(4 * k + e) / MT][(4 * k + e) % MT] = q[e] * kSumScale;
                 }
 #pragma unroll
                 for (int i = 0; i < NO; ++i) chk[c] = __builtin_fmaf(o[i / MT][i % MT], 0.0f, chk[c]);

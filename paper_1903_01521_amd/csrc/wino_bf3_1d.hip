@@ -25,6 +25,25 @@ namespace wino {
 // 112x112 200 -> 85, N = 32 1x5 256 -> 256 at 28x28 104 -> 62.
 constexpr int kL1FB = 2, kL1TB = 2, kL1Waves = 4;
 
+// bt8 times kSplitScale (powers of two: the same rounding), 3 operations more.
+__device__ __forceinline__ void bt8_scaled(const float (&d)[8], float (&v)[8]) {
+    constexpr float S = kSplitScale;
+    const float s5 = S * d[5], s6 = S * d[6], s7 = S * d[7];
+    v[0] = __builtin_fmaf(5.25f * S, d[2] - d[4], __builtin_fmaf(-S, d[0], s6));
+    v[7] = __builtin_fmaf(5.25f * S, d[3] - d[5], __builtin_fmaf(-S, d[1], s7));
+    const float s15 = __builtin_fmaf(S, d[1], s5), s26 = __builtin_fmaf(S, d[2], s6);
+    v[1] = __builtin_fmaf(-4.25f * S, d[3] + d[4], s15 + s26);
+    v[2] = __builtin_fmaf(4.25f * S, d[3] - d[4], s26 - s15);
+    const float o3 = __builtin_fmaf(0.5f * S, d[1], __builtin_fmaf(-2.5f * S, d[3], 2.0f * s5));
+    const float e3 = __builtin_fmaf(0.25f * S, d[2], __builtin_fmaf(-1.25f * S, d[4], s6));
+    v[3] = e3 + o3;
+    v[4] = e3 - o3;
+    const float o5 = __builtin_fmaf(2.0f * S, d[1], __builtin_fmaf(-2.5f * S, d[3], 0.5f * s5));
+    const float e5 = __builtin_fmaf(4.0f * S, d[2], __builtin_fmaf(-5.0f * S, d[4], s6));
+    v[5] = e5 + o5;
+    v[6] = e5 - o5;
+}
+
 template <int MT, int AX>
 __global__ __launch_bounds__(256, 2) void k_bf3_1d(const float* __restrict__ x, const char* __restrict__ US,
                                                    const float* __restrict__ U, float* __restrict__ y, Geom g, int nkg,
@@ -101,7 +120,7 @@ __global__ __launch_bounds__(256, 2) void k_bf3_1d(const float* __restrict__ x, 
             float d[8], v[8];
 #pragma unroll
             for (int u = 0; u < 8; ++u) d[u] = AX == 2 || (in >> u & 1) ? xd[j][u] : 0.0f;
-            bt8(d, v);
+            bt8_scaled(d, v);
             uint32_t* const o = vdst + stage * (T * TB * 512) + (uq + j * (4 / TB)) * 64;
 #pragma unroll
             for (int t = 0; t < T; ++t) {
@@ -192,9 +211,9 @@ __global__ __launch_bounds__(256, 2) void k_bf3_1d(const float* __restrict__ x, 
     }
     if (!work) return;
 
-    // Outputs of the 16 filters of block kb from their products m; true where one
-    // of them is not finite (before ReLU).
-    auto store = [&](const TileCoord& ot, int kb, const f32x4 (&m)[T]) -> bool {
+    // Outputs of the 16 filters of block kb from their products m, times scale;
+    // true where one of them is not finite (before ReLU).
+    auto store = [&](const TileCoord& ot, int kb, const f32x4 (&m)[T], float scale) -> bool {
         float chk = 0.0f;                              // NaN once an output is not finite
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
@@ -204,7 +223,10 @@ __global__ __launch_bounds__(256, 2) void k_bf3_1d(const float* __restrict__ x, 
             for (int t = 0; t < T; ++t) a[t] = m[t][r];
             at8<MT>(a, o);
 #pragma unroll
-            for (int i = 0; i < MT; ++i) chk = __builtin_fmaf(o[i], 0.0f, chk);
+            for (int i = 0; i < MT; ++i) {
+                o[i] *= scale;
+                chk = __builtin_fmaf(o[i], 0.0f, chk);
+            }
             if (!ot.valid || k >= g.K) continue;
             float* yk = y + ((size_t)ot.n * g.K + k) * g.Ho * g.Wo;
 #pragma unroll
@@ -235,7 +257,7 @@ __global__ __launch_bounds__(256, 2) void k_bf3_1d(const float* __restrict__ x, 
         const TileCoord ot = decode_tile((tp * TB + b) * 16 + (lane & 15), g);
 #pragma unroll
         for (int f = 0; f < FB; ++f)
-            if (__any(store(ot, kbw + f, acc[f][b]))) redo |= 1u << (b * FB + f);
+            if (__any(store(ot, kbw + f, acc[f][b], kSumScale))) redo |= 1u << (b * FB + f);
     }
     // An operand that is infinite or NaN has no split: every result it enters is
     // NaN here.  Such blocks (and those whose sums overflow) run once more on
@@ -269,7 +291,7 @@ __global__ __launch_bounds__(256, 2) void k_bf3_1d(const float* __restrict__ x, 
                 for (int e = 0; e < 4; ++e) m[4 * g4 + e] = mfma16x16x4(u[e], v[4 * g4 + e], m[4 * g4 + e]);
             }
         }
-        store(ot, kb, m);
+        store(ot, kb, m, 1.0f);
     }
 }
 

@@ -33,8 +33,14 @@ __device__ __forceinline__ f32x4 mfma16x16x32(uint4 a, uint4 b, f32x4 c) {
 
 // ------------------------------------------------------------------ exact split
 // A fp32 value as three bf16 terms, h + m + l, eight significand bits each: the
-// operands of the kernels that run fp32 products on the bf16 matrix cores.
+// operands of the kernels that run fp32 products on the bf16 matrix cores.  They
+// split 2^16 times the value: bf16's smallest number is 2^-133, fp32's 2^-149, so
+// that of unscaled values below 2^-110 l, and below 2^-118 m, would lose bits (x of
+// 1e-36 gave errors of 3e-5).  Products carry 2^32, taken out of the sums.  At the
+// other end values from 2^112 and sums from 2^96 overflow, which the check for
+// results that are not finite catches.
 constexpr uint32_t kHi16 = 0xffff0000u;
+constexpr float kSplitScale = 65536.0f, kSumScale = 1.0f / (65536.0f * 65536.0f);
 
 // (X, Y) of one value, h and m cut off towards zero; low half first:
 // X = (m, h), Y = (h, l).
@@ -86,7 +92,7 @@ __device__ __forceinline__ void store_v3(char* __restrict__ blk, int q, int lane
         for (int e = 0; e < 4; ++e) r[e] = __float_as_uint(v[4 * g4 + e]);
         transpose_rows(r);
 #pragma unroll
-        for (int d = 0; d < 4; ++d) split3(__uint_as_float(r[d]), X[d], Y[d]);
+        for (int d = 0; d < 4; ++d) split3(__uint_as_float(r[d]) * kSplitScale, X[d], Y[d]);
         *(uint4*)(p + g4 * 4 * kUsBytes + i * 16) = make_uint4(X[0], X[1], X[2], X[3]);
         *(uint2*)(p + g4 * 4 * kUsBytes + 1024 + i * 8) = make_uint2(__builtin_amdgcn_perm(Y[1], Y[0], 0x07060302u),
                                                                      __builtin_amdgcn_perm(Y[3], Y[2], 0x07060302u));

@@ -189,7 +189,7 @@ __global__ __launch_bounds__(512) void k_gemm3(const char* __restrict__ US, cons
 #pragma unroll
             for (int r = 0; r < 4; ++r) chk = __builtin_fmaf(acc[f][b][r], 0.0f, chk);
             if (kbw + f < g.KB && pb0 + b < g.PB)
-                *(f32x4*)(M + (((size_t)(pb0 + b) * g.KB + kbw + f) * T + tg * 4 + we) * 256 + lane * 4) = acc[f][b];
+                *(f32x4*)(M + (((size_t)(pb0 + b) * g.KB + kbw + f) * T + tg * 4 + we) * 256 + lane * 4) = acc[f][b] * kSumScale;
         }
         if (__any(chk != chk)) redo |= 1u << b;
     }

@@ -8,6 +8,7 @@ import pytest
 import torch
 
 import gpu_helpers as h
+from oracle import direct
 from paper_1903_01521_amd import binding as B
 
 pytestmark = pytest.mark.gpu
@@ -102,3 +103,32 @@ def test_nonfinite_filters(name):
     flat[-1, -1] = -float("inf")                   # the last filter's last tap
     flat[1, 2] = 3.0e38
     assert not np.isfinite(same(name, x, g, 0)).all()
+
+
+def err2(y, ref):
+    d = y.astype(np.float64) - ref
+    return float(np.sqrt((d * d).sum() / (ref * ref).sum()))
+
+
+# powers of two that x and the filters are scaled by: the smallest that keep every
+# output a normal number, U below 2^-126, values past 2^112 and sums past 2^96
+SCALES = [(0, 0), (-110, 0), (-120, 0), (0, -110), (0, -118), (60, -118), (-124, 60), (110, -30), (100, 0)]
+
+
+@pytest.mark.parametrize("name", ["bf3_f4", "bf3_f2", "bf3_5x5", "g3_f2", "g3_nhwc", "1d_w", "1d_h"])
+def test_small_and_large_scales(name):
+    # AUTO's 2-norm error is no larger than the three stages' (measured 0.86-0.89
+    # of it at scale 1; 1.05 leaves room for values that scaling made subnormal),
+    # at every scale of the inputs.
+    entry, _, _, _, _, _, pad, m, r = LAYERS[name][:9]
+    x0, g0 = make(name)
+    xd = x0.permute(0, 3, 1, 2) if entry == "nhwc" else x0
+    g4 = g0[:, :, None] if entry == "w" else g0[..., None] if entry == "h" else g0
+    pads = ((0, 0), (0, 0), (0 if entry == "w" else pad,) * 2, (0 if entry == "h" else pad,) * 2)
+    ref0 = direct.conv2d(np.pad(h.host(xd), pads), np.ascontiguousarray(h.host(g4)), 0)
+    for sx, sg in SCALES:
+        x, g = x0 * 2.0 ** sx, g0 * 2.0 ** sg
+        ref = ref0 * 2.0 ** (sx + sg)
+        e, e3 = err2(run(name, x, g, 0), ref), err2(run(name, x, g, B.WINO_ALGO_STAGED), ref)
+        print(f"  {name} x 2^{sx} g 2^{sg}: {e:.2e}, three stages {e3:.2e}", flush=True)
+        assert e <= 1.05 * e3
