@@ -140,9 +140,12 @@ extern "C" {
  * larger than the fp32 kernels'.  Infinite and NaN
  * inputs (and sums that overflow, here from 2^96) give what those kernels give, also with
  * WINO_FLAG_RELU: the 16-tile x 16-filter blocks with a result that is not finite
- * are computed once more on fp32 MFMA.  The filters' split goes to the workspace
- * (6 bytes per element of U, with the channels in whole steps of 16) in every
- * call; without that workspace AUTO runs the kernels below.  An explicitly
+ * are computed once more on fp32 MFMA.  The filters' split
+ * (6 bytes per element of U, with the channels in whole steps of 16) goes to the
+ * workspace in every call.  AUTO asks for exactly that where it would else run
+ * the fused kernel, for the workspace of the split algorithm or of the 1-D
+ * stages where it would else run those, and for the split U, the split V and M
+ * on deep layers; with less than it asks for it runs the kernels below.  An explicitly
  * chosen algorithm always runs on fp32 MFMA. */
 
 /* Human-readable text of a status code (static storage, never NULL). */

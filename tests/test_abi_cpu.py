@@ -57,6 +57,19 @@ def test_workspace_bytes():
     assert B.wino_workspace_bytes(1, 64, 112, 112, 64, 1, 4, 0x500) == 2**64 - 1
 
 
+def test_workspace_bytes_on_the_bf16_matrix_cores():
+    # In place of the fused kernel: the filters' split, 6 bytes per element of U
+    # with the channels in whole steps of 16.  In place of the split algorithm:
+    # that algorithm's workspace.
+    N, C, H, W, K, m = 33, 64, 56, 56, 64, 4
+    assert B.wino_plan_r(N, C, H, W, K, 1, m, 3, 0)[1] == B.WINO_ALGO_FUSED
+    assert B.wino_workspace_bytes(N, C, H, W, K, 1, m, 0) == 6 * 36 * 64 * 64
+    N, C, H, W, K, m = 64, 256, 56, 56, 256, 4
+    assert B.wino_plan_r(N, C, H, W, K, 1, m, 3, 0)[1] == B.WINO_ALGO_SPLIT
+    assert B.wino_workspace_bytes(N, C, H, W, K, 1, m, 0) == \
+        B.wino_workspace_bytes(N, C, H, W, K, 1, m, B.WINO_ALGO_SPLIT) > 6 * 36 * 256 * 256
+
+
 GOOD = dict(N=1, C=4, H=8, W=8, K=4, pad=1, m=4)
 
 

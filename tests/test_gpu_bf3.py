@@ -5,8 +5,10 @@ kernel's tiles: filters, channels and tiles that leave remainders in the
 last tile's columns past the image), images of which several share a block of
 tiles, a single channel step, and F(4x4,3x3), F(2x2,3x3), F(2x2,5x5).
 
-A layer runs this kernel when AUTO asks for exactly the filters' split as
-workspace: 6 bytes per element of U with the channels in whole steps of 16.
+In place of the fused kernel AUTO asks for exactly the filters' split as
+workspace, 6 bytes per element of U with the channels in whole steps of 16, which
+shows that this kernel runs; in place of the split algorithm it asks for that
+algorithm's workspace, and a result that differs from that algorithm's shows it.
 
 Tolerances: the gates of the fp32 paths.  The split drops products below
 2^-21 of |u v| (2^-24 on average), inside fp32 rounding; on integers whose
@@ -37,6 +39,8 @@ SHAPES = [
     (31, 37, 27, 25, 140, 2, 3),    # odd
     (16, 48, 35, 35, 64, 2, 5),     # 5x5, odd
     (41, 39, 34, 36, 60, 2, 5),     # 5x5, whole tiles
+    (16, 100, 27, 25, 144, 2, 3),   # in place of the split algorithm
+    (48, 100, 27, 25, 144, 4, 3),
 ]
 
 
@@ -47,16 +51,25 @@ def _conv(x, g, m, r, flags=0):
     U = h.empty_bytes(B.wino_filter_bytes_r(C, K, m, r))
     B.check(B.wino_filter_transform_r(h.dev(g), U, C, K, m, r))
     wsb = B.wino_workspace_bytes_r(N, C, H, W, K, pad, m, r, flags)
-    assert wsb == split_bytes(C, K, m, r), "the layer runs on the bf16 matrix cores"
-    ws, y = h.empty_bytes(wsb), h.empty_bytes(4 * N * K * H * W)
-    y.fill_(float("nan"))
-    B.check(B.wino_conv2d_r(h.dev(x), U, y, N, C, H, W, K, pad, m, r, flags, ws, wsb))
-    return h.host(y).reshape(N, K, H, W)
+    ws, xd = h.empty_bytes(wsb), h.dev(x)
+
+    def run(flags):
+        y = h.empty_bytes(4 * N * K * H * W)
+        B.check(B.wino_conv2d_r(xd, U, y, N, C, H, W, K, pad, m, r, flags, ws, wsb))
+        return h.host(y).reshape(N, K, H, W)
+
+    y = run(flags)
+    st, algo, _ = B.wino_plan_r(N, C, H, W, K, pad, m, r, flags)
+    assert st == B.WINO_OK
+    if algo == B.WINO_ALGO_SPLIT:
+        assert not np.array_equal(y, run(flags | algo)), "the layer runs on the bf16 matrix cores"
+    else:
+        assert wsb == split_bytes(C, K, m, r), "the layer runs on the bf16 matrix cores"
+    return y
 
 
-def _reference(x, g, r, absval=False):
-    return direct.conv2d(x, g, r // 2, absval=absval) if r == 3 else \
-        direct.conv2d(x, g, r // 2, absval=absval)
+def _reference(x, g, r):
+    return direct.conv2d(x, g, r // 2)
 
 
 @pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
@@ -96,3 +109,27 @@ def test_bf3_range(scale):
     x = (rng.standard_normal((N, C, H, W)) * scale).astype(np.float32)
     g = (rng.standard_normal((K, C, r, r)) * np.sqrt(2.0 / (9 * C))).astype(np.float32)
     assert h.normwise_err(_conv(x, g, m, r), _reference(x, g, r)) <= TOL[m]
+
+
+@pytest.mark.parametrize("shape", [SHAPES[4], SHAPES[8]], ids=["fused", "split"])
+def test_bf3_without_its_workspace(shape):
+    # a byte less than AUTO asks for: the fused kernel
+    N, C, H, W, K, m, r = shape
+    print(f"bf3 without workspace shape={shape}", flush=True)
+    st, algo, _ = B.wino_plan_r(N, C, H, W, K, r // 2, m, r, 0)
+    assert st == B.WINO_OK and algo == (B.WINO_ALGO_FUSED if shape == SHAPES[4] else B.WINO_ALGO_SPLIT)
+    rng = np.random.default_rng(7)
+    x = h.dev(rng.standard_normal((N, C, H, W)))
+    g = h.dev(rng.standard_normal((K, C, r, r)) * np.sqrt(2.0 / (r * r * C)))
+    U = h.empty_bytes(B.wino_filter_bytes_r(C, K, m, r))
+    B.check(B.wino_filter_transform_r(g, U, C, K, m, r))
+    wsb = B.wino_workspace_bytes_r(N, C, H, W, K, r // 2, m, r, 0)
+    ws = h.empty_bytes(wsb)
+    out = {}
+    for name, flags, w, n in (("exact", 0, ws, wsb), ("short", 0, ws, wsb - 1), ("none", 0, None, 0),
+                              ("fused", B.WINO_ALGO_FUSED, None, 0)):
+        y = h.empty_bytes(4 * N * K * H * W)
+        B.check(B.wino_conv2d_r(x, U, y, N, C, H, W, K, r // 2, m, r, flags, w, n))
+        out[name] = h.host(y)
+    assert np.array_equal(out["short"], out["fused"]) and np.array_equal(out["none"], out["fused"])
+    assert not np.array_equal(out["exact"], out["fused"])
