@@ -175,6 +175,12 @@ size_t slice_workspace(const Geom& g, int nsl) {
 // cores instead where their estimate is 5% shorter (the estimates are that
 // good); with less workspace than that needs, the kernel it was given to runs.
 constexpr double kBf3Margin = 0.95;
+// Not below 12 channels: what the split drops is then as large as the fp32 sums'
+// rounding.  2-norm errors against the fp32 kernels': F(2x2,3x3) 5 channels 1.32e-7
+// and 1.17e-7, 8 1.31 and 1.28, 10 1.20 and 1.19 (x >= 0), 12 1.34 and 1.42;
+// F(2x2,5x5) 5 9.3e-7 and 7.9e-7, 10 9.7 and 9.6, 12 9.7 and 9.9; 1-D 8 3.54e-7 and
+// 3.46e-7 (1x5), 12 4.2 and 4.4 (1x7).
+constexpr int kSplitMinChannels = 12;
 // fused_ns leaves out a round's fixed part (2.5 us: what the measured times of
 // 27 layers from 10 to 72 us lie above it at least).
 double fused_full_ns(const Geom& g, FusedCfg c) { return fused_ns(g, c) + 2500.0 * rounds(fused_workgroups(g, c)); }
@@ -266,7 +272,7 @@ double staged_ns(const Geom& g, bool g3) {
 // (deep layers with few tiles: many filters to share a transformed input, so
 // that writing and reading V and M costs less than transforming again).
 void choose_g3(const Geom& g, unsigned flags, Plan* p) {
-    if (!p->automatic || g.axis != 0 || p->algo == WINO_ALGO_LOWC || (flags & ~WINO_FLAG_RELU) || !gemm3_takes(g)) return;
+    if (!p->automatic || g.axis != 0 || g.C < kSplitMinChannels || (flags & ~WINO_FLAG_RELU) || !gemm3_takes(g)) return;
     if (!g.nhwc && !block_images_fit(g)) return;
     if (p->algo == WINO_ALGO_FUSED && (p->cfg.csplit > 1 || p->cfg.nsl > 1)) return;   // rounds less often
     const double base = p->bf3 ? bf3_ns(g)
@@ -285,11 +291,8 @@ void choose_g3(const Geom& g, unsigned flags, Plan* p) {
 // 16-channel step where few workgroups run.  With few tiles and many channels
 // they win (N = 1 192-channel 17x17: 22 against 30 us), as the one kernel's steps
 // take 2 us each; else the one kernel (N = 3 33 -> 50 at 101x37: 22 -> 15 us).
-// Not below 12 channels: what the split drops is then as large as the fp32
-// sums' rounding (8 channels, 1x5: 3.54e-7 against 3.46e-7 from the exact
-// result, 5 channels, 1x3: 3.6e-7 against 3.3e-7; 12, 1x7: 4.2e-7 against 4.4e-7).
 bool choose_bf3_1d(const Geom& g, const Plan& p) {
-    if (!p.automatic || g.axis == 0 || g.C < 12 || !bf3_1d_takes(g) || us_bytes(g) > stage_bytes(g)) return false;
+    if (!p.automatic || g.axis == 0 || g.C < kSplitMinChannels || !bf3_1d_takes(g) || us_bytes(g) > stage_bytes(g)) return false;
     const double x = 4.0 * g.N * g.C * g.H * g.W, y = 4.0 * g.N * g.K * g.Ho * g.Wo;
     const double gemm = 2.0 * g.T * g.P * (double)g.C * g.K / 105000.0, chain = 800.0 * ((g.CQ + 3) / 4);
     const double stages = 14500.0 + (x + 4.0 * v_elems(g)) / 4800.0 + (4.0 * m_elems(g) + y) / 5600.0 +
@@ -413,14 +416,16 @@ int make_plan_unchecked(const Geom& g, unsigned flags, Plan* p) {
         p->algo = WINO_ALGO_SPLIT;
     if (p->algo == WINO_ALGO_SPLIT) {
         p->need = split_workspace(g);
-        p->bf3 = p->automatic && bf3_takes(g) && bf3_workspace(g) <= p->need && bf3_ns(g) < kBf3Margin * split_ns(g);
+        p->bf3 = p->automatic && g.C >= kSplitMinChannels && bf3_takes(g) && bf3_workspace(g) <= p->need &&
+                 bf3_ns(g) < kBf3Margin * split_ns(g);
         return WINO_OK;
     }
     // Not where the fused kernel splits the channels over waves: summed in parts
     // it rounds less often than one chain of three bf16 products per 16
     // channels (1.6e-6 against 1.8e-6 from the exact result at 112 channels,
     // F(4x4); unsplit 2.0e-6).
-    if (p->automatic && !cs_req && !blk && c.csplit == 1 && bf3_takes(g) && bf3_ns(g) < kBf3Margin * fused_full_ns(g, c)) {
+    if (p->automatic && !cs_req && !blk && c.csplit == 1 && g.C >= kSplitMinChannels && bf3_takes(g) &&
+        bf3_ns(g) < kBf3Margin * fused_full_ns(g, c)) {
         p->bf3 = true;
         p->need = bf3_workspace(g);
         return WINO_OK;

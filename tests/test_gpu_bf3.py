@@ -133,3 +133,26 @@ def test_bf3_without_its_workspace(shape):
         out[name] = h.host(y)
     assert np.array_equal(out["short"], out["fused"]) and np.array_equal(out["none"], out["fused"])
     assert not np.array_equal(out["exact"], out["fused"])
+
+
+@pytest.mark.parametrize("shape", [(16, 11, 35, 35, 160, 2, 3), (8, 11, 112, 112, 160, 2, 3), (32, 11, 17, 17, 160, 2, 5),
+                                   (64, 11, 35, 35, 64, 4, 3)], ids=lambda s: "x".join(map(str, s)))
+def test_few_channels_run_on_fp32(shape):
+    # below 12 channels the dropped products are as large as the fp32 kernels'
+    # own rounding: AUTO is the fp32 algorithm that wino_plan_r names
+    N, C, H, W, K, m, r = shape
+    print(f"few channels shape={shape}", flush=True)
+    rng = np.random.default_rng(8)
+    x = h.dev(rng.standard_normal((N, C, H, W)))
+    g = h.dev(rng.standard_normal((K, C, r, r)) * np.sqrt(2.0 / (r * r * C)))
+    U = h.empty_bytes(B.wino_filter_bytes_r(C, K, m, r))
+    B.check(B.wino_filter_transform_r(g, U, C, K, m, r))
+    st, algo, _ = B.wino_plan_r(N, C, H, W, K, r // 2, m, r, 0)
+    assert st == B.WINO_OK
+    out = []
+    for flags in (0, algo):
+        wsb = B.wino_workspace_bytes_r(N, C, H, W, K, r // 2, m, r, flags)
+        y = h.empty_bytes(4 * N * K * H * W)
+        B.check(B.wino_conv2d_r(x, U, y, N, C, H, W, K, r // 2, m, r, flags, h.empty_bytes(wsb), wsb))
+        out.append(h.host(y))
+    assert np.array_equal(*out)
