@@ -285,19 +285,19 @@ void choose_g3(const Geom& g, unsigned flags, Plan* p) {
 }
 
 // AUTO's choice for 1-D layers: the one kernel on the bf16 matrix cores where it
-// is estimated 15% shorter than the three stages, whose workspace holds the
-// filters' split.  The stages of 16 layers took 14.5 us of launches and
-// latencies, the transforms' bytes, and GEMMs at 105 TFLOP/s or 0.8 us per
-// 16-channel step where few workgroups run.  With few tiles and many channels
-// they win (N = 1 192-channel 17x17: 22 against 30 us), as the one kernel's steps
-// take 2 us each; else the one kernel (N = 3 33 -> 50 at 101x37: 22 -> 15 us).
+// is estimated 5% shorter than the three stages, whose workspace holds the
+// filters' split.  The stages' estimate is fitted to 1640 layers (84-114% of it in
+// 90 of 100): launches and latencies, the transforms' bytes, the GEMMs, and the
+// steps' latency.  The smallest layers stay with them (N = 9 48 -> 96 at 8x16, 7x1:
+// 12 us against 14, N = 3 48 -> 272 at 14x14, 1x5: 12 against 15), and deep ones of
+// few tiles (N = 4 512 -> 400 at 19x57, 7x1: 95 against 103), as the one kernel's
+// steps take 1.6 us each; else the one kernel (N = 3 33 -> 50 at 37x101: 22 -> 14).
 bool choose_bf3_1d(const Geom& g, const Plan& p) {
     if (!p.automatic || g.axis == 0 || g.C < kSplitMinChannels || !bf3_1d_takes(g) || us_bytes(g) > stage_bytes(g)) return false;
     const double x = 4.0 * g.N * g.C * g.H * g.W, y = 4.0 * g.N * g.K * g.Ho * g.Wo;
-    const double gemm = 2.0 * g.T * g.P * (double)g.C * g.K / 105000.0, chain = 800.0 * ((g.CQ + 3) / 4);
-    const double stages = 14500.0 + (x + 4.0 * v_elems(g)) / 4800.0 + (4.0 * m_elems(g) + y) / 5600.0 +
-                          (gemm > chain ? gemm : chain);
-    return bf3_1d_ns(g) < 0.85 * stages;
+    const double stages = 9900.0 + (x + 4.0 * v_elems(g)) / 4400.0 + (4.0 * m_elems(g) + y) / 3000.0 +
+                          2.0 * g.T * g.P * (double)g.C * g.K / 137000.0 + 280.0 * ((g.CQ + 3) / 4);
+    return bf3_1d_ns(g) < kBf3Margin * stages;
 }
 
 // The plan, or WINO_ERR_UNSUPPORTED where its input kernels' offsets would not

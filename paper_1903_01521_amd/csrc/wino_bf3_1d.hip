@@ -329,12 +329,15 @@ hipError_t launch_bf3_1d(const float* x, const float* U, float* y, void* ws, con
     return hipErrorInvalidValue;
 }
 
-// Estimated time: the filters' split and the launches, then 2 us per step of
-// every 256 workgroups (two of a CU overlap, but a step of the pair takes twice
-// as long; one alone takes as long, its filter loads' latency).
+// Estimated time, fitted to 1640 layers (74-121% of it in 90 of 100): the filters'
+// split, the launches and the last workgroups' outputs (m along the axis, rows
+// apart along H), then 1.6 us per step of every 256 workgroups (two of a CU
+// overlap, but a step of the pair takes twice as long; one alone takes as long,
+// its filter loads' latency) and their outputs.
 double bf3_1d_ns(const Geom& g) {
-    const double rounds = bf3_1d_items(g) / 256.0, steps = (g.CQ + 3) / 4;
-    return 8000.0 + (rounds > 1.0 ? rounds : 1.0) * (500.0 + 2000.0 * steps);
+    const double items = bf3_1d_items(g) / 256.0, rounds = items > 1.0 ? items : 1.0, steps = (g.CQ + 3) / 4;
+    const double first = g.m == 6 ? 2800.0 : g.m == 4 ? 1100.0 : 0.0, more = g.m == 6 ? 4900.0 : g.m == 4 ? 3000.0 : 1300.0;
+    return 8800.0 + first + (g.axis == 2 ? 800.0 : 0.0) + 1600.0 * rounds * steps + more * (rounds - 1.0);
 }
 
 }  // namespace wino

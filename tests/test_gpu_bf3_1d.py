@@ -6,7 +6,9 @@ before the tensor or end past it, padding wider than the region, odd widths,
 tensors that are only 4-byte aligned, every (m, r), either axis.
 
 The explicit three stages round differently, so a result that differs from
-theirs shows that AUTO ran this kernel.  Tolerance: the gate of the 1-D paths."""
+theirs shows that AUTO ran this kernel; on the smallest layers, where they are
+faster (10.9 against 9.4 to 14 us), AUTO's result is theirs.  Tolerance: the gate of
+the 1-D paths."""
 import numpy as np
 import pytest
 
@@ -18,15 +20,23 @@ pytestmark = pytest.mark.gpu
 
 # (N, C, H, W, K, pad, m, r)
 SHAPES = [
-    (1, 16, 14, 14, 16, 3, 2, 7),       # one workgroup, one step
+    (60, 16, 14, 14, 16, 3, 2, 7),      # one step
     (3, 33, 37, 101, 50, 3, 2, 7),      # odd sizes, 3 steps
     (2, 20, 57, 58, 130, 0, 4, 5),      # no padding, two filter groups, the last with one block
-    (2, 17, 9, 20, 40, 9, 6, 3),        # regions wholly outside the image
-    (2, 17, 9, 1, 16, 7, 2, 7),         # one column: regions that begin rows before the tensor
-    (5, 13, 7, 3, 7, 2, 4, 5),          # images smaller than a tile row
+    (100, 17, 9, 20, 40, 9, 6, 3),      # regions wholly outside the image
+    (200, 17, 9, 1, 16, 7, 2, 7),       # one column: regions that begin rows before the tensor
+    (1200, 13, 7, 3, 7, 2, 4, 5),       # images smaller than a tile row
     (64, 48, 28, 29, 272, 1, 6, 3),     # three filter groups, several rounds of workgroups
     (40, 420, 28, 28, 500, 1, 6, 3),    # 27 steps
     (30, 491, 25, 29, 500, 2, 4, 5),    # 31 steps
+]
+SMALL = [
+    (1, 16, 14, 14, 16, 3, 2, 7),
+    (2, 17, 9, 20, 40, 9, 6, 3),
+    (2, 17, 9, 1, 16, 7, 2, 7),
+    (5, 13, 7, 3, 7, 2, 4, 5),
+    (2, 48, 24, 24, 112, 1, 6, 3),
+    (9, 48, 8, 16, 96, 3, 2, 7),
 ]
 
 
@@ -59,7 +69,7 @@ def _case(shape, axis):
 
 
 @pytest.mark.parametrize("axis", ["w", "h"])
-@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("shape", SHAPES + SMALL, ids=lambda s: "x".join(map(str, s)))
 def test_bf3_1d_edges(shape, axis):
     print(f"bf3 1-D shape={shape} axis={axis}", flush=True)
     pad, m, r = shape[5:]
@@ -70,5 +80,5 @@ def test_bf3_1d_edges(shape, axis):
     staged = _run(x, g, pad, m, r, axis, B.WINO_FLAG_RELU | B.WINO_ALGO_STAGED)
     print(f"  normwise err {err:.2e}, three stages {h.normwise_err(staged, ref):.2e}", flush=True)
     assert err <= 1e-3
-    assert not np.array_equal(y, staged), "the layer runs in one kernel"
+    assert np.array_equal(y, staged) == (shape in SMALL), "which layers run in one kernel"
     assert np.array_equal(y, _run(x, g, pad, m, r, axis, B.WINO_FLAG_RELU, shift=1))   # 4-byte aligned tensors
