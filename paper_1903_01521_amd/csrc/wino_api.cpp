@@ -181,9 +181,15 @@ constexpr double kBf3Margin = 0.95;
 // F(2x2,5x5) 5 9.3e-7 and 7.9e-7, 10 9.7 and 9.6, 12 9.7 and 9.9; 1-D 8 3.54e-7 and
 // 3.46e-7 (1x5), 12 4.2 and 4.4 (1x7).
 constexpr int kSplitMinChannels = 12;
-// fused_ns leaves out a round's fixed part (2.5 us: what the measured times of
-// 27 layers from 10 to 72 us lie above it at least).
-double fused_full_ns(const Geom& g, FusedCfg c) { return fused_ns(g, c) + 2500.0 * rounds(fused_workgroups(g, c)); }
+// What the fused kernel takes, for the choice between it and the kernels on the
+// bf16 matrix cores: fused_ns leaves out a round's fixed part and is too high where
+// rounds are many (1178 layers that AUTO then gave those: 5x5 87-108% of this in
+// 90 of 100, where fused_ns and 2.5 us a round were 107-123% of what was measured;
+// F(2x2,3x3) 91-110%).
+double fused_full_ns(const Geom& g, FusedCfg c) {
+    const double f = fused_ns(g, c), r = rounds(fused_workgroups(g, c));
+    return g.r == 5 ? 2900.0 + 0.83 * f + 3400.0 * r : g.m == 2 ? 1600.0 + 0.72 * f + 4900.0 * r : f + 2500.0 * r;
+}
 
 // The three stages' workspace: V and M, and for the GEMMs on the bf16 matrix
 // cores the split filters, the split V and M.
@@ -253,19 +259,26 @@ bool plan_fits(const Geom& g, const Plan& p) {
 
 int make_plan_unchecked(const Geom& g, unsigned flags, Plan* p);
 
-// Estimated times of the three stages: the transforms' bytes at the rates they
-// reach (4.8 and 5.6 TB/s), and the GEMMs, in fp32 at 105 TFLOP/s, or on the
-// bf16 matrix cores (g3) in rounds of one workgroup per CU, 2.1 us per 16-channel
-// step (the chip's clock falls to 1.6 GHz under them) and 3 us for M's stores,
-// after the filters' split.  g3 measured 249 us on the 32-image 512-channel
-// 28x28 layer (here 241) and 102 us at 14x14 with F(2x2) (here 112).
+// Estimated times of the three stages.  fp32: the transforms' bytes at the rates
+// they reach (4.8 and 5.6 TB/s) and the GEMMs at 105 TFLOP/s (189 channel-last
+// layers took 86-110% of it).  On the bf16 matrix cores (g3), fitted to 1460
+// layers (88-115% of it in 90 of 100): the transforms' bytes at 4.3 and 3.1 TB/s,
+// the filters' split, and the GEMMs in rounds of one workgroup per CU, 1.7 us per
+// 16-channel step (the chip's clock falls to 1.6 GHz under them) and 2.4 us for
+// M's stores, or V's and M's bytes at 4 TB/s.  No 5x5 layer took less than 33 us
+// and no F(2x2,3x3) one less than 38; F(4x4,3x3) ones lost where the other kernels
+// take less than 50 (N = 64 164 -> 208 at 9x9: 43 -> 51).
 double staged_ns(const Geom& g, bool g3) {
     const double x = 4.0 * g.N * g.C * g.H * g.W, y = 4.0 * g.N * g.K * g.Ho * g.Wo, m = 4.0 * m_elems(g);
-    const double v = g3 ? (double)v3_bytes(g) : 4.0 * v_elems(g);
-    const double in = 2000.0 + (x + v) / 4800.0, out = 2000.0 + (m + y) / 5600.0;
-    if (!g3) return in + out + 2000.0 + 2.0 * g.T * g.P * (double)g.C * g.K / 105000.0;
-    const double steps = (g.CQ + 3) / 4, gemm = rounds(gemm3_items(g)) * (3000.0 + 2100.0 * steps);
-    return in + out + 1000.0 + 10.0 * 256.0 * g.T * g.KB * steps / 6000.0 + (gemm > (v + m) / 3200.0 ? gemm : (v + m) / 3200.0);
+    if (!g3) {
+        const double in = (x + 4.0 * v_elems(g)) / 4800.0, out = (m + y) / 5600.0;
+        return 15200.0 + 0.945 * (in + out + 2.0 * g.T * g.P * (double)g.C * g.K / 105000.0);
+    }
+    const double v = (double)v3_bytes(g), steps = (g.CQ + 3) / 4;
+    const double gemm = rounds(gemm3_items(g)) * (2400.0 + 1700.0 * steps), mem = (v + m) / 4000.0;
+    const double t = 7000.0 + (x + v) / 4300.0 + us_bytes(g) / 3600.0 + (gemm > mem ? gemm : mem) + (m + y) / 3100.0;
+    const double least = g.r == 5 ? 33000.0 : g.m == 2 ? 38000.0 : 50000.0;
+    return t < least ? least : t;
 }
 
 // AUTO's last choice: the three stages with the GEMMs on the bf16 matrix cores
@@ -275,11 +288,14 @@ void choose_g3(const Geom& g, unsigned flags, Plan* p) {
     if (!p->automatic || g.axis != 0 || g.C < kSplitMinChannels || (flags & ~WINO_FLAG_RELU) || !gemm3_takes(g)) return;
     if (!g.nhwc && !block_images_fit(g)) return;
     if (p->algo == WINO_ALGO_FUSED && (p->cfg.csplit > 1 || p->cfg.nsl > 1)) return;   // rounds less often
+    // split_ns is 112% of what F(2x2) took (540 layers), without a fixed part
     const double base = p->bf3 ? bf3_ns(g)
-                      : p->algo == WINO_ALGO_SPLIT ? split_ns(g)
+                      : p->algo == WINO_ALGO_SPLIT ? 9500.0 + (g.m == 2 ? 0.84 : 0.92) * split_ns(g)
                       : p->algo == WINO_ALGO_STAGED ? staged_ns(g, false)
                                                     : fused_full_ns(g, p->cfg);
-    if (staged_ns(g, true) >= 0.9 * base) return;
+    // 0.97: of 1102 layers near the line, 26 that run g3 are slower by more than 3% (at
+    // most 9%), and 75 that do not would be faster by that; at 1.0 43 and 44, up to 14%.
+    if (staged_ns(g, true) >= 0.97 * base) return;
     p->g3 = true;
     p->need3 = stage3_bytes(g);
 }

@@ -70,6 +70,21 @@ def test_workspace_bytes_on_the_bf16_matrix_cores():
         B.wino_workspace_bytes(N, C, H, W, K, 1, m, B.WINO_ALGO_SPLIT) > 6 * 36 * 256 * 256
 
 
+@pytest.mark.parametrize("N, C, H, W, K, pad, m, r", [
+    (18, 144, 29, 63, 448, 1, 2, 5),      # 421 us, on the bf16 matrix cores 456
+    (23, 112, 67, 67, 464, 0, 2, 5),      # 1109, 1196
+    (1, 336, 161, 161, 160, 0, 2, 5),     # 337, 366
+    (60, 502, 16, 18, 372, 2, 2, 3),      # 289, 331
+    (58, 480, 25, 26, 245, 0, 2, 3),      # 327, 362
+])
+def test_auto_stays_on_fp32_where_it_is_faster(N, C, H, W, K, pad, m, r):
+    # AUTO asks for the workspace of the fp32 algorithm that wino_plan_r names
+    st, algo, slices = B.wino_plan_r(N, C, H, W, K, pad, m, r, 0)
+    assert st == B.WINO_OK and slices == 1
+    assert B.wino_workspace_bytes_r(N, C, H, W, K, pad, m, r, 0) == \
+        B.wino_workspace_bytes_r(N, C, H, W, K, pad, m, r, algo)
+
+
 GOOD = dict(N=1, C=4, H=8, W=8, K=4, pad=1, m=4)
 
 
