@@ -11,12 +11,16 @@ shows that this kernel runs; in place of the split algorithm it asks for that
 algorithm's workspace, and a result that differs from that algorithm's shows it.
 
 Tolerances: the gates of the fp32 paths.  The split drops products below
-2^-21 of |u v| (2^-24 on average), inside fp32 rounding; on integers whose
-terms fit 16 bits nothing is dropped and the result is the oracle's exactly."""
+2^-21 of |u v| (2^-24 on average), inside fp32 rounding, so that the 2-norm error
+is no larger than the explicit fp32 algorithm's (1.05 of it is allowed; a wrong
+third term exceeds it some hundred times); on integers whose terms fit 16 bits
+nothing is dropped and the result is the oracle's exactly, nor where one side has
+more bits and the other fits 8."""
 import numpy as np
 import pytest
 
 import gpu_helpers as h
+from test_gpu_bf3_values import err2
 from oracle import direct
 from paper_1903_01521_amd import binding as B
 
@@ -44,7 +48,7 @@ SHAPES = [
 ]
 
 
-def _conv(x, g, m, r, flags=0):
+def _conv(x, g, m, r, flags=0, with_fp32=False):
     N, C, H, W = x.shape
     K = g.shape[0]
     pad = r // 2
@@ -58,14 +62,22 @@ def _conv(x, g, m, r, flags=0):
         B.check(B.wino_conv2d_r(xd, U, y, N, C, H, W, K, pad, m, r, flags, ws, wsb))
         return h.host(y).reshape(N, K, H, W)
 
+    def run_at(shift):                       # x and y off 16-byte alignment by floats
+        xs = h.dev(np.concatenate([np.full(shift, np.nan, np.float32), x.ravel()]))[shift:]
+        y = h.empty_bytes(4 * (N * K * H * W + shift))
+        B.check(B.wino_conv2d_r(xs, U, y[shift:], N, C, H, W, K, pad, m, r, flags, ws, wsb))
+        return h.host(y)[shift:].reshape(N, K, H, W)
+
     y = run(flags)
     st, algo, _ = B.wino_plan_r(N, C, H, W, K, pad, m, r, flags)
     assert st == B.WINO_OK
+    y32 = run(flags | algo)
     if algo == B.WINO_ALGO_SPLIT:
-        assert not np.array_equal(y, run(flags | algo)), "the layer runs on the bf16 matrix cores"
+        assert not np.array_equal(y, y32), "the layer runs on the bf16 matrix cores"
     else:
         assert wsb == split_bytes(C, K, m, r), "the layer runs on the bf16 matrix cores"
-    return y
+    assert np.array_equal(y, run_at(1))
+    return (y, y32) if with_fp32 else y
 
 
 def _reference(x, g, r):
@@ -79,12 +91,13 @@ def test_bf3_edges(shape):
     rng = np.random.default_rng(sum(shape))
     x = rng.standard_normal((N, C, H, W)).astype(np.float32)
     g = (rng.standard_normal((K, C, r, r)) * np.sqrt(2.0 / (r * r * C))).astype(np.float32)
-    y = _conv(x, g, m, r, B.WINO_FLAG_RELU)
+    y, y32 = _conv(x, g, m, r, B.WINO_FLAG_RELU, with_fp32=True)
     ref = np.maximum(_reference(x, g, r), 0.0)
     assert np.all(np.isfinite(y))
     err = h.normwise_err(y, ref)
-    print(f"  normwise err {err:.2e}", flush=True)
+    print(f"  normwise err {err:.2e}, 2-norm {err2(y, ref):.2e}, fp32 {err2(y32, ref):.2e}", flush=True)
     assert err <= (1e-3 if r == 5 else TOL[m])
+    assert err2(y, ref) <= 1.05 * err2(y32, ref)
     assert np.array_equal(y, _conv(x, g, m, r, B.WINO_FLAG_RELU))      # bitwise run to run
 
 
@@ -97,6 +110,38 @@ def test_bf3_exact_on_integers(shape):
     rng = np.random.default_rng(5)
     x = rng.integers(-1, 2, (N, C, H, W)).astype(np.float32)
     g = (rng.integers(-1, 2, (K, C, r, r)) * (576 if m == 4 else 4)).astype(np.float32)
+    assert np.array_equal(_conv(x, g, m, r).astype(np.float64), _reference(x, g, r))
+
+
+def wide_inputs(N, C, H, W, K, side):
+    """Integers of F(2x2,3x3) whose transformed filters (side "u") or inputs ("v")
+    need three terms, with every sum below 2^24 in units of its last bit."""
+    rng = np.random.default_rng(9)
+    odd = lambda shape, top: ((2 * rng.integers(0, top // 2, shape) + 1) * rng.choice([-1, 1], shape)).astype(np.float32)
+    x, g = np.zeros((N, C, H, W), np.float32), np.zeros((K, C, 3, 3), np.float32)
+    if side == "u":
+        # |U| < 9 * 2^15; a region's four pixels of every third row and column, each in one
+        # channel: |M| < 2^20.2, their nine in an output < 2^23.4
+        g[:] = 4 * odd(g.shape, 1 << 15)
+        i, j = np.meshgrid(range(0, H, 3), range(0, W, 3), indexing="ij")
+        for n in range(N):
+            x[n, rng.integers(0, C, i.shape), i, j] = rng.choice([-1, 1], i.shape)
+    else:
+        # |V| < 2^18, U in 0, 1, 2, 4 from one tap in each of two channels: an output's
+        # nine |M| add up to at most 2 * 16 * 2^18
+        x[:] = odd(x.shape, 1 << 16)
+        for k in range(K):
+            for c in rng.choice(C, 2, replace=False):
+                g[k, c, rng.integers(3), rng.integers(3)] = 4 * rng.choice([-1, 1])
+    return x, g
+
+
+@pytest.mark.parametrize("side", ["u", "v"])
+@pytest.mark.parametrize("shape", [SHAPES[4], SHAPES[5]], ids=lambda s: "x".join(map(str, s)))
+def test_bf3_exact_on_wide_integers(shape, side):
+    N, C, H, W, K, m, r = shape
+    print(f"bf3 wide integers shape={shape} side={side}", flush=True)
+    x, g = wide_inputs(N, C, H, W, K, side)
     assert np.array_equal(_conv(x, g, m, r).astype(np.float64), _reference(x, g, r))
 
 
