@@ -3,8 +3,8 @@
 //
 // v_mfma_f32_16x16x4_f32 runs at 1/16 of the rate of v_mfma_f32_16x16x32_bf16.
 // A fp32 value's 24 significand bits are exactly h + m + l, three bf16 values
-// of 8 bits each (h and m cut off or rounded, l what is left).  u*v is then the sum of nine products, of which
-// the six largest,
+// of 8 bits each (h and m cut off or rounded, l what is left).  u*v is then the
+// sum of nine products, of which the six largest,
 //     hh + hm + mh + hl + mm + lh,
 // leave an error below 2^-21 |u v| (the dropped ml + lm + ll; about 2^-24 on
 // average), no more than fp32 accumulation over the channels adds.  Six
@@ -21,9 +21,10 @@
 namespace wino {
 
 // ------------------------------------------------------------------ split U
-// The same with h and m rounded to nearest (h only where that cannot
-// overflow): m and l then have either sign, so that the dropped products of
-// the filters' terms with an input's cut-off ones average out.
+// (X, Y) of one value as split3 gives them (for the inputs), but with h and m
+// rounded to nearest (h only where that cannot overflow): m and l then have either
+// sign, so that the dropped products of the filters' terms with an input's
+// cut-off ones average out.
 __device__ __forceinline__ void split3_rounded(float v, uint32_t& X, uint32_t& Y) {
     const uint32_t vb = __float_as_uint(v);
     const uint32_t hb = (vb & 0x7f800000u) < 0x7f000000u ? vb + 0x8000u : vb;
@@ -141,8 +142,8 @@ __device__ __forceinline__ void bf3_bt(const float (&a)[6], float (&r)[6]) {
 
 template <int MT, int R, bool RAG>
 __global__ __launch_bounds__(512) void k_bf3(const float* __restrict__ x, const char* __restrict__ US,
-                                             const float* __restrict__ U, float* __restrict__ y, Geom g, FusedTiling ft, int relu, int vec_ok,
-                                             int nts) {
+                                             const float* __restrict__ U, float* __restrict__ y, Geom g,
+                                             FusedTiling ft, int relu, int vec_ok, int nts) {
     using S = Bf3Shape<MT, R>;
     constexpr int A = S::A, T = S::T, HN = S::HN, NP = S::NP, FB = S::FB, TB = S::TB, D = S::D, UN = S::UN, PAD = S::PAD;
     __shared__ uint4 vs[S::VB / 16];
@@ -151,8 +152,7 @@ __global__ __launch_bounds__(512) void k_bf3(const float* __restrict__ x, const 
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int item = (blockIdx.x & 7) * ft.per + (blockIdx.x >> 3);
     if (item >= ft.nt * ft.nkg) return;
-    const int kgi = ft.kfast ? item % ft.nkg : item / ft.nt;
-    const int tp = ft.kfast ? item / ft.nkg : item - kgi * ft.nt;
+    const int kgi = item % ft.nkg, tp = item / ft.nkg;      // filter group fastest
     const int wp = wave & 3, wf = wave >> 2;
     const int nsteps = ft.nsteps;
 
@@ -528,7 +528,6 @@ static hipError_t bf3_instance(const float* x, const float* U, float* y, void* w
     ft.nkg = (g.KB + S::KGW - 1) / S::KGW;
     ft.per = (int)(((long)ft.nt * ft.nkg + 7) / 8);
     ft.nsteps = c16;
-    ft.kfast = 1;
     const dim3 grid((unsigned)(8 * ft.per)), block(512);
     const int vec_ok = (g.Wo % MT == 0) && aligned(y, 4 * MT);
     if (g.W % MT == 0)
