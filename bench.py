@@ -44,6 +44,7 @@ import numpy as np
 HBM_PEAK = 8.0e12          # B/s, MI355X HBM3E
 FP32_MFMA_PEAK = 157.3e12  # FLOP/s, MI355X dense fp32 matrix
 FP16_MFMA_PEAK = 2.5e15    # FLOP/s, MI355X dense fp16 / bf16 matrix
+SPLIT_MFMA_PEAK = FP16_MFMA_PEAK / 6   # fp32 products as six bf16 ones (operands split in three terms)
 COPY_BYTES = 64 << 20      # size of the plain copy that calibrates the byte counters
 EVICT_BYTES = 512 << 20    # read before each cold launch: twice the 256 MB last-level cache
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -69,6 +70,13 @@ KERNEL_NAMES = {"filter": "void wino::k_filter", "fused": "void wino::k_fused", 
                 # blocked V, then the GEMMs storing y channel-last
                 "split_nhwc": ("void wino::k_vrows_nhwc|void wino::k_input_nhwc4|void wino::k_input_nhwc",
                                "void wino::k_gemm_out"),
+                # fp32 layers on the bf16 matrix cores: the filters' split, then the layer in one
+                # kernel (2-D, 1-D), or the three stages around k_gemm3
+                "bf3": ("void wino::k_usplit", "void wino::k_bf3"),
+                "bf3_1d": ("void wino::k_usplit", "void wino::k_bf3_1d"),
+                "g3": ("void wino::k_usplit",
+                       "void wino::k_vrows|void wino::k_input|void wino::k_vrows_nhwc|void wino::k_input_nhwc",
+                       "void wino::k_gemm3", "void wino::k_output|void wino::k_output_nhwc"),
                 # the fused kernel over channel slices, then the sum of the slices
                 "fused_sliced": ("void wino::k_fused", "void wino::k_slice_sum")}
 
@@ -136,18 +144,30 @@ def layer_numbers(N, L):
         "gemm_out": v_b + u_b + y_b,
         # the 16-bit input transform (16-bit V written)
         "input16": x_b + v_b // 2,
+        # fp32 layers on the bf16 matrix cores: the filters' split (6 bytes an
+        # element, written and read) before the one kernel; with k_gemm3 the split
+        # V too, and M
+        "bf3": x_b + 4 * u_b + y_b,
+        "bf3_1d": x_b + 4 * u_b + y_b,
+        "g3": x_b + 3 * v_b + 4 * u_b + 2 * m_b + y_b,
+        "usplit": u_b + 3 * u_b // 2,
+        "input3": x_b + 3 * v_b // 2,
+        "gemm3": 3 * v_b // 2 + 3 * u_b // 2 + m_b,
     }
     f["flops"] = {"fused": f["gemm_flops"], "fused_sliced": f["gemm_flops"], "split": f["gemm_flops"],
                   "split_nhwc": f["gemm_flops"], "gemm": f["gemm_flops"], "gemm_out": f["gemm_flops"],
                   "stages": f["gemm_flops"],
-                  "stages16": f["gemm_flops"], "gemm16": f["gemm_flops"], "split16": f["gemm_flops"]}
+                  "stages16": f["gemm_flops"], "gemm16": f["gemm_flops"], "split16": f["gemm_flops"],
+                  "bf3": f["gemm_flops"], "bf3_1d": f["gemm_flops"], "g3": f["gemm_flops"], "gemm3": f["gemm_flops"]}
     return f
 
 
 def roofline(kind, nums, seconds):
     b = nums["bytes"].get(kind, 0)
     fl = nums["flops"].get(kind, 0)
-    peak = FP16_MFMA_PEAK if kind in ("stages16", "gemm16", "split16") else FP32_MFMA_PEAK   # the GEMM's own operand type
+    peak = (FP16_MFMA_PEAK if kind in ("stages16", "gemm16", "split16")
+            else SPLIT_MFMA_PEAK if kind in ("bf3", "bf3_1d", "g3", "gemm3")
+            else FP32_MFMA_PEAK)                                           # the GEMM's own operand type
     t_hbm = b / HBM_PEAK
     t_mfma = fl / peak
     if t_mfma >= t_hbm and fl > 0:
@@ -164,7 +184,7 @@ def roofline(kind, nums, seconds):
 def traffic_file(workload: str, kind: str) -> str:
     """Counter summary of a workload's convolution kernel (fused, low-C), or of
     one stage of its staged path (input, gemm, output)."""
-    if kind in ("fused", "fused_sliced", "split", "split_nhwc", "lowc"):
+    if kind in ("fused", "fused_sliced", "split", "split_nhwc", "lowc", "bf3", "bf3_1d", "g3"):
         return os.path.join(PROFILES, f"traffic_{workload}.txt")
     return os.path.join(PROFILES, f"traffic_{workload}_{kind}.txt")
 
@@ -245,13 +265,17 @@ def mfma_summary(args):
     kg = sum(mean("GRBM_GUI_ACTIVE", p)[0] for p in prefixes)
     ki = sum(mean("SQ_INSTS_MFMA", p)[0] for p in prefixes)
     kn = min(mean("SQ_INSTS_MFMA", p)[1] for p in prefixes)
-    need = sum(f["flops"].get(kind, 0) for f in nums) / len(nums) / (2 * 16 * 16 * 4)
+    # fp32 products per instruction: 16x16x4 in fp32; split, three 16x16x32 bf16 ones do 16 channels
+    split3 = kind in ("bf3", "bf3_1d", "g3")
+    inst = "v_mfma_f32_16x16x32_bf16" if split3 else "v_mfma_f32_16x16x4_f32"
+    need = sum(f["flops"].get(kind, 0) for f in nums) / len(nums) / (2 * 16 * 16 * (16 / 3 if split3 else 4))
     fl = f" --flags {args.flags:#x}" if args.flags is not None else ""
     lines = [
         f"# MFMA work and utilisation of the {kind} launch on workload {name}, from one",
         "# rocprofv3 PMC run of bench.py on one MI355X (command below).",
-        "#   mfma_insts: v_mfma_f32_16x16x4_f32 per launch, all waves (SQ_INSTS_MFMA);",
-        "#   mfma_insts_algorithmic: the launch's algorithmic FLOPs / 2048;",
+        f"#   mfma_insts: {inst} per launch, all waves (SQ_INSTS_MFMA);",
+        "#   mfma_insts_algorithmic: the launch's algorithmic FLOPs / 2048"
+        + (" * 3 / 4 (three per 16 channels);" if split3 else ";"),
         "#   busy_cycles_per_inst: SQ_VALU_MFMA_BUSY_CYCLES / SQ_INSTS_MFMA;",
         "#   util_active: busy cycles / (GRBM_GUI_ACTIVE / 8 XCDs * 1024 SIMDs), and the",
         "#   same for the MFMA probe in this run (its share of the published peak).",
@@ -383,7 +407,8 @@ def trace_summary(args):
 
 
 # Stage of a kernel of the step, by name (the first prefix that matches).
-STAGE_OF = (("k_gemm_out", "gemm_out"), ("k_gemm16", "gemm16"), ("k_gemm", "gemm"), ("k_fused", "fused"),
+STAGE_OF = (("k_gemm_out", "gemm_out"), ("k_gemm16", "gemm16"), ("k_gemm3", "gemm3"), ("k_gemm", "gemm"),
+            ("k_usplit", "usplit"), ("k_bf3_1d", "bf3_1d"), ("k_bf3", "bf3"), ("k_fused", "fused"),
             ("k_slice_sum", "slice_sum"), ("k_lowc", "lowc"), ("k_maxpool2x2", "maxpool"),
             ("k_vrows", "input"), ("k_vblk", "input"), ("k_input", "input"), ("k_output", "output"))
 STAGE_MARKER = "FillFunctor"      # the torch fill that --stage-trace launches before every launch
@@ -427,7 +452,8 @@ def stage_table(args):
              "# sequence, so every kernel runs after its real predecessor), and its fraction",
              "# of its own roofline from the algorithmic FLOPs or bytes of its stage",
              "# (input/output transforms and pools: HBM bytes; GEMMs: MFMA FLOPs or HBM",
-             "# bytes, whichever bounds them; peaks 157.3 TFLOP/s fp32, 8 TB/s).",
+             "# bytes, whichever bounds them; peaks 157.3 TFLOP/s fp32, 2500 / 6 where fp32",
+             "# operands are split into three bf16 terms, 8 TB/s).",
              "# commands (on the GPU host; <repo> is the repository root):",
              "#   cd /tmp && export TMPDIR=/tmp",
              f"#   rocprofv3 --kernel-trace --output-format csv -d <out>/st -o run -- python3 <repo>/bench.py "
@@ -447,6 +473,8 @@ def stage_table(args):
         stage = next((st for pre, st in STAGE_OF if base.startswith(pre)), None)
         if stage == "input" and prec:
             stage = "input16"
+        if stage == "input" and any(n.startswith("k_gemm3") for (i, _), (n, _) in per.items() if i == li):
+            stage = "input3"
         med, p10, p90 = float(np.median(ns)), float(np.percentile(ns, 10)), float(np.percentile(ns, 90))
         total_ns += med
         if stage != "maxpool":
@@ -497,8 +525,9 @@ def planner_layers():
 
 def read_planner_table(path=PLANNER_TABLE):
     """Rows of the committed planner table: dict per layer with the shape, the
-    measured time (us) of every algorithm the library accepted for it, and
-    AUTO's choice when the table was taken."""
+    measured time (us) of every algorithm the library accepted for it and of AUTO
+    itself (which may run the layer on the bf16 matrix cores), and the algorithm
+    that wino_plan_r named when the table was taken."""
     rows = []
     for line in open(path):
         if line.startswith("#") or not line.strip() or line.startswith("N ") or ":" in line.split()[0]:
@@ -509,7 +538,8 @@ def read_planner_table(path=PLANNER_TABLE):
         for kv in f[7:-2]:
             k, v = kv.split("=")
             times[k] = float(v)
-        rows.append(dict(shape=shape, times=times, best=f[-2], auto=f[-1]))
+        auto_us = times.pop("AUTO", None)
+        rows.append(dict(shape=shape, times=times, auto_us=auto_us, best=f[-2], auto=f[-1]))
     return rows
 
 
@@ -531,7 +561,9 @@ def planner_table(args):
     lines = ["# Planner table: per-layer time (us, one wino_conv2d call, HIP graph of 10 back-to-back",
              "# calls, median of 5 replays) of every algorithm the library accepts for the layer",
              "# (fused: the planner's fused variant without channel slices; fused_sN: with N slices;",
-             "# split; staged; lowc), the fastest, and AUTO's choice (wino_plan_r) when taken.",
+             "# split; staged; lowc), all on fp32 MFMA, then of AUTO (with its own workspace; it",
+             "# may run on the bf16 matrix cores), the fastest algorithm, and the one that",
+             "# wino_plan_r named when taken.",
              "# one MI355X; command (on the GPU host, from the repository root):",
              "#   python3 bench.py --planner-table --write-summary",
              f"sources_sha256: {sources_hash()}",
@@ -572,7 +604,8 @@ def planner_table(args):
         auto = planner_candidate_name(algo, nsl)
         cands = [("fused", B.WINO_ALGO_FUSED)] + [(f"fused_s{n}", B.WINO_ALGO_FUSED | B.WINO_CSLICES(n))
                                                   for n in (2, 4)] + [
-            ("split", B.WINO_ALGO_SPLIT), ("staged", B.WINO_ALGO_STAGED), ("lowc", B.WINO_ALGO_LOWC)]
+            ("split", B.WINO_ALGO_SPLIT), ("staged", B.WINO_ALGO_STAGED), ("lowc", B.WINO_ALGO_LOWC),
+            ("AUTO", B.WINO_ALGO_AUTO)]
         times = {}
         for cname, fl in cands:
             wsb = B.wino_workspace_bytes(N, C, H, W, K, pad, m, fl)
@@ -587,7 +620,7 @@ def planner_table(args):
                   B.wino_conv2d(x, U, y, N, C, H, W, K, pad, m, fl, ws if wsb else None, wsb, sp))
             times[cname] = time_us(fn)
             del ws
-        best = min(times, key=times.get)
+        best = min((k for k in times if k != "AUTO"), key=times.get)
         log(f"planner N={N} C={C} {H}x{W} K={K} m={m}: " +
             " ".join(f"{k}={v:.1f}" for k, v in times.items()) + f"  best {best} auto {auto}")
         lines.append(f"{N} {C} {H} {W} {K} {pad} {m}  " + " ".join(f"{k}={v:.1f}" for k, v in times.items())
@@ -599,6 +632,49 @@ def planner_table(args):
         with open(PLANNER_TABLE, "w") as fh:
             fh.write(text)
     print(text, end="")
+
+
+def split3_kind(N, L, flags, wsb):
+    """The kind of launch where AUTO runs an fp32 layer on the bf16 matrix cores,
+    else None (needs a GPU).  wino_plan_r and the workspace name the algorithm that
+    those kernels stand in for; with k_gemm3, or in place of the fused kernel, AUTO
+    asks for a workspace of its own, and in place of the split algorithm or the 1-D
+    stages its results are not that algorithm's bit for bit."""
+    import torch
+    from paper_1903_01521_amd import binding as B
+    if flags & ~B.WINO_FLAG_RELU:
+        return None
+    f = layer_numbers(N, L)
+    up = lambda v, a: -(-v // a) * a
+    KB, PB, C16 = -(-L.K // 16), -(-f["P"] // 16), -(-L.C // 16)
+    us, v3 = KB * C16 * f["T"] * 1536, PB * C16 * f["T"] * 1536
+    if L.axis == "" and wsb == up(us, 256) + up(v3, 256) + PB * KB * f["T"] * 1024:
+        return "g3"
+    if L.nhwc:
+        return None
+    algo = B.WINO_ALGO_STAGED if L.axis else B.wino_plan_r(N, L.C, L.H, L.W, L.K, L.pad, L.m, L.r, flags)[1]
+    if algo == B.WINO_ALGO_FUSED:
+        return "bf3" if wsb == us else None
+    if algo == B.WINO_ALGO_LOWC:
+        return None
+    x = torch.randn(N * L.C * L.H * L.W, device="cuda:0")
+    g = torch.randn(L.K * L.C * (L.r if L.axis else L.r * L.r), device="cuda:0")
+    ub = B.wino_filter_bytes_1d(L.C, L.K, L.m, L.r) if L.axis else B.wino_filter_bytes_r(L.C, L.K, L.m, L.r)
+    U, ws = torch.empty(ub // 4, device="cuda:0"), torch.empty(max(wsb // 4, 1), device="cuda:0")
+    out = []
+    for fl in (flags, flags | algo):
+        y = torch.empty(N * L.K * f["Ho"] * f["Wo"], device="cuda:0")
+        if L.axis:
+            B.check(B.wino_filter_transform_1d(g, U, L.C, L.K, L.m, L.r))
+            B.check(B.wino_conv2d_1d(x, U, y, N, L.C, L.H, L.W, L.K, L.pad, L.m, L.r, AXIS[L.axis], fl, ws, wsb))
+        else:
+            B.check(B.wino_filter_transform_r(g, U, L.C, L.K, L.m, L.r))
+            B.check(B.wino_conv2d_r(x, U, y, N, L.C, L.H, L.W, L.K, L.pad, L.m, L.r, fl, ws, wsb))
+        out.append(y)
+    torch.cuda.synchronize()
+    if torch.equal(*out):
+        return None
+    return "bf3_1d" if L.axis else "bf3"
 
 
 def sleep_calibration(stream) -> float:
@@ -754,16 +830,18 @@ def main():
                 split_wsb = B.wino_workspace_bytes_nhwc(N, L.C, L.H, L.W, L.K, L.pad, L.m,
                                                         (flags & ~B.WINO_ALGO_MASK) | B.WINO_ALGO_SPLIT)
                 kind = "split_nhwc" if wsb == split_wsb and (flags & B.WINO_ALGO_MASK) != B.WINO_ALGO_STAGED else "stages"
+                kind = split3_kind(N, L, flags | relu, wsb) or kind
                 out.append((f"L{i}.conv", i, kind, (lambda sp, i=i, L=L, a=a, relu=relu, ws=ws, wsb=wsb:
                                                          B.wino_conv2d_nhwc(a, Us[i], ys[i], N, L.C, L.H, L.W, L.K,
                                                                             L.pad, L.m, flags | relu, ws, wsb, sp))))
                 a = ys[i]
                 continue
-            if L.axis:                     # 1-D layer: the three stages in one call
+            if L.axis:                     # 1-D layer: the three stages in one call, or one kernel
                 ws, wsb = wss[i]
+                kind = split3_kind(N, L, flags | relu, wsb) or "stages"
                 out.append((f"L{i}.filter", i, "filter", (lambda sp, i=i, L=L: B.wino_filter_transform_1d(
                     hg[i], Us[i], L.C, L.K, L.m, L.r, sp))))
-                out.append((f"L{i}.conv", i, "stages", (lambda sp, i=i, L=L, a=a, relu=relu, ws=ws, wsb=wsb:
+                out.append((f"L{i}.conv", i, kind, (lambda sp, i=i, L=L, a=a, relu=relu, ws=ws, wsb=wsb:
                                                          B.wino_conv2d_1d(a, Us[i], ys[i], N, L.C, L.H, L.W, L.K,
                                                                           L.pad, L.m, L.r, AXIS[L.axis],
                                                                           flags | relu, ws, wsb, sp))))
@@ -791,6 +869,7 @@ def main():
                 else:
                     kind = {B.WINO_ALGO_LOWC: "lowc", B.WINO_ALGO_SPLIT: "split"}.get(
                         algo, "fused_sliced" if nsl > 1 else "fused")
+                    kind = split3_kind(N, L, flags | relu, wsb) or kind
                 out.append((f"L{i}.conv", i, kind, (lambda sp, i=i, L=L, a=a, relu=relu, ws=ws, wsb=wsb:
                                                        B.wino_conv2d_r(a, Us[i], ys[i], N, L.C, L.H, L.W, L.K,
                                                                        L.pad, L.m, L.r, flags | relu,

@@ -132,21 +132,22 @@ extern "C" {
 #define WINO_CSLICES(n)    (((unsigned)(n) & 0xFu) << 20)
 
 /* WINO_ALGO_AUTO runs large fp32 "same" layers (pad (r-1)/2, NCHW), deep ones
- * (also channel-last) and most 1-D ones on the bf16 matrix cores: U and V are split exactly into three bf16 terms each (24
- * significand bits; scaled by 2^16, so that every fp32 value below 2^112 has
- * its split, down to the smallest) and the six largest of the
- * nine products are summed in fp32, for 2.67 times the fp32 matrix rate.  The
- * dropped products are below 2^-21 of |u v|; errors against 64 bits are no
- * larger than the fp32 kernels'.  Infinite and NaN
- * inputs (and sums that overflow, here from 2^96) give what those kernels give, also with
- * WINO_FLAG_RELU: the 16-tile x 16-filter blocks with a result that is not finite
- * are computed once more on fp32 MFMA.  The filters' split
- * (6 bytes per element of U, with the channels in whole steps of 16) goes to the
- * workspace in every call.  AUTO asks for exactly that where it would else run
- * the fused kernel, for the workspace of the split algorithm or of the 1-D
- * stages where it would else run those, and for the split U, the split V and M
- * on deep layers; with less than it asks for it runs the kernels below.  An explicitly
- * chosen algorithm always runs on fp32 MFMA. */
+ * (also channel-last) and 1-D ones but the smallest, all of at least 12 channels,
+ * on the bf16 matrix cores: U and V are split exactly into three bf16 terms each
+ * (24 significand bits; scaled by 2^16, so that every fp32 value below 2^112 has
+ * its split, down to the smallest) and the six largest of the nine products are
+ * summed in fp32, for 2.67 times the fp32 matrix rate.  The dropped products are
+ * below 2^-21 of |u v|; errors against 64 bits are no larger than the fp32
+ * kernels'.  Infinite and NaN inputs (and sums that overflow, here from 2^96) give
+ * what those kernels give, also with WINO_FLAG_RELU: the 16-tile x 16-filter blocks
+ * with a result that is not finite are computed once more on fp32 MFMA.  The
+ * filters' split (6 bytes per element of U, with the channels in whole steps of
+ * 16) goes to the workspace in every call.  AUTO asks for exactly that where it
+ * would else run the fused kernel, for the workspace of the split algorithm or of
+ * the 1-D stages where it would else run those, and for the split U, the split V
+ * and M on deep layers; with less than it asks for it runs the algorithm that
+ * wino_plan_r names, or the fused kernel.  An explicitly chosen algorithm always
+ * runs on fp32 MFMA. */
 
 /* Human-readable text of a status code (static storage, never NULL). */
 const char* wino_status_string(int status);
@@ -255,9 +256,11 @@ int wino_filter_transform_p(const float* g, void* U, int C, int K, int m, unsign
  *   A^T = [1 1 1 1 1 0; 0 1 -1 2 -2 1]
  *   y[n,k,i,j] = sum_c sum_{r,s<5} x[n,c,i+r-pad,j+s-pad] * g[k,c,r,s].
  * Layouts of U, V and M are the ones above with T = 36.  g is [K][C][5][5].
- * 5x5 layers run the fused kernel (WINO_ALGO_AUTO or _FUSED, no workspace;
- * WINO_BLOCK_* and WINO_CSPLIT(n), n in {1,2,4}, as for m = 4) or the three
- * stages (WINO_ALGO_STAGED, with the workspace), plus WINO_FLAG_RELU.
+ * 5x5 layers run the fused kernel (WINO_ALGO_AUTO or _FUSED; WINO_BLOCK_* and
+ * WINO_CSPLIT(n), n in {1,2,4}, as for m = 4) or the three stages
+ * (WINO_ALGO_STAGED, with the workspace), plus WINO_FLAG_RELU.  _FUSED takes no
+ * workspace; AUTO asks for one for channel slices and where it runs a layer on the
+ * bf16 matrix cores (see WINO_ALGO_AUTO), and without it runs the fused kernel.
  * Errors as for the 3x3 calls; UNSUPPORTED for other (m, r), for
  * WINO_ALGO_SPLIT and _LOWC, and for the 16-bit formats. */
 size_t wino_filter_bytes_r(int C, int K, int m, int r);
@@ -291,8 +294,10 @@ int wino_output_transform_r(const float* M, float* y, int N, int K, int H, int W
  *           Ho = H + 2*pad - (r-1), Wo = W; tiles of m x 1 outputs.
  * Tile p = (n*th + ti)*tw + tj as above (th = Ho, tw = ceil(Wo/m) along W;
  * th = ceil(Ho/m), tw = Wo along H); U, V and M use the blocked layouts above
- * with T = 8.  The three stages run (flags: WINO_ALGO_AUTO or _STAGED, and
- * WINO_FLAG_RELU); the workspace is always required.  Errors as for
+ * with T = 8.  Flags: WINO_ALGO_STAGED (the three stages), WINO_ALGO_AUTO (one
+ * kernel on the bf16 matrix cores where that is faster, see WINO_ALGO_AUTO, else
+ * the three stages) and WINO_FLAG_RELU.  The workspace, the stages' V and M, is
+ * always required.  Errors as for
  * wino_conv2d; UNSUPPORTED for other (m, r) or axis values. */
 #define WINO_AXIS_W 1
 #define WINO_AXIS_H 2
@@ -312,9 +317,12 @@ int wino_conv2d_1d(const float* x, const float* U, float* y,
  * WINO_ALGO_SPLIT the split path (input transform into the tile-blocked V
  * workspace, then GEMMs with the output transform storing y channel-last);
  * WINO_ALGO_AUTO takes split on layers with at least two rounds of its work
- * items on the CUs (e.g. N=64, 256 channels, 56x56), else the three stages;
- * and WINO_FLAG_RELU.  wino_workspace_bytes_nhwc gives the workspace of the
- * plan the flags choose.  Errors as for wino_conv2d. */
+ * items on the CUs (e.g. N=64, 256 channels, 56x56), else the three stages, and
+ * on deep layers the three stages with the GEMMs on the bf16 matrix cores where
+ * that is faster (see WINO_ALGO_AUTO above; with less than their workspace split
+ * or the stages, in the workspace of those); and WINO_FLAG_RELU.
+ * wino_workspace_bytes_nhwc gives the workspace of the plan the flags choose.
+ * Errors as for wino_conv2d. */
 size_t wino_workspace_bytes_nhwc(int N, int C, int H, int W, int K, int pad, int m, unsigned flags);
 int wino_conv2d_nhwc(const float* x, const float* U, float* y,
                      int N, int C, int H, int W, int K, int pad, int m,
@@ -328,9 +336,10 @@ int wino_conv2d_nhwc(const float* x, const float* U, float* y,
  * holds on every GPU it runs on until the process ends (no hipMalloc, hipFree
  * or other allocation; the caller passes x, U and y as before).
  *   - WINO_ALGO_AUTO plans as wino_conv2d does with a workspace of that size:
- *     the split algorithm, channel slices or the staged one where their
- *     workspace fits, else the fused kernel (WINO_ERR_WORKSPACE only when no
- *     algorithm that fits is left, see the size limits above).
+ *     the split algorithm, channel slices, the staged one or the kernels on the
+ *     bf16 matrix cores where their workspace fits, else the fused kernel
+ *     (WINO_ERR_WORKSPACE only when no algorithm that fits is left, see the size
+ *     limits above).
  *   - An explicit algorithm or WINO_CSLICES(n) whose workspace
  *     (wino_workspace_bytes with the same flags) exceeds the array returns
  *     WINO_ERR_WORKSPACE before any HIP call.

@@ -91,9 +91,9 @@ __global__ __launch_bounds__(256) void k_usplit(const float* __restrict__ U, cha
 // the outer region columns from the neighbouring lanes instead of by loads of
 // their own 540.  2^16 in B^T and 2^-32 and the check in the epilogue cost 1-2%
 // (582 -> 590, N = 32 64-channel 224x224 354 -> 363).
-// Against fp32 MFMA kernels: N = 32 64-channel 224x224 532 -> 352 us, N = 32
-// 128-channel 112x112 427 -> 293, N = 32 512-channel 14x14 F(2x2) 143 -> 128,
-// N = 64 256-channel 56x56 616 -> 578, N = 32 5x5 48 -> 64 at 35x35 50 -> 40.
+// Against fp32 MFMA kernels, both timed in turn: N = 32 64-channel 224x224 536 ->
+// 375 us, N = 32 128-channel 112x112 417 -> 310, N = 64 256-channel 56x56 645 -> 560,
+// N = 32 5x5 48 -> 64 at 35x35 50 -> 39.
 template <int MT, int R>
 struct Bf3Shape {
     static constexpr int A = MT + R - 1, T = A * A, HN = A / 2, NP = HN * HN, PAD = (R - 1) / 2;
@@ -507,8 +507,9 @@ bool bf3_takes(const Geom& g) {
 
 // One workgroup per CU: rounds of a fixed part (first loads and transform,
 // exchange, stores) and the 16-channel steps, as measured (F(4x4): 7 rounds of
-// 16 steps 540 us, 13 of 4 360 us; F(2x2,5x5): two of 3 40 us; F(2x2): one of
-// 32 steps 121 us), after the filters' split.
+// 16 steps 560 us, 13 of 4 375 us; F(2x2,5x5): two of 3 39 us; F(2x2): one of
+// 32 steps 121 us), after the filters' split.  889 layers took 84-112% of it in 90
+// of 100.
 double bf3_ns(const Geom& g) {
     const double steps = (g.CQ + 3) / 4, rounds = (double)((bf3_items(g) + 255) / 256);
     const double split = 3000.0 + 10.0 * 256.0 * g.T * g.KB * steps / 5000.0;

@@ -20,9 +20,9 @@ namespace wino {
 // size (its accumulators move between the two register files: 39 -> 68 us on
 // the first layer below), and so was one with 64 tiles (99 us).  Two 16-byte
 // loads of the 8 inputs along W instead of eight of 4 bytes: 302 -> 279 us on the
-// second.  Against the three stages (fp32 GEMMs): N = 32 1x7 192 -> 160 at 17x17
-// 52 -> 40 us, N = 64 1x3 512 -> 512 at 28x28 416 -> 279, N = 16 1x7 64 -> 64 at
-// 112x112 200 -> 85, N = 32 1x5 256 -> 256 at 28x28 104 -> 62.
+// second.  Against the three stages (fp32 GEMMs), both timed in turn: N = 32 1x7
+// 192 -> 160 at 17x17 48 -> 37 us (7x1 42), N = 64 1x3 512 -> 512 at 28x28 415 -> 282,
+// N = 16 1x7 64 -> 64 at 112x112 192 -> 87, N = 32 1x5 256 -> 256 at 28x28 98 -> 57.
 constexpr int kL1FB = 2, kL1TB = 2, kL1Waves = 4;
 
 // bt8 times kSplitScale (powers of two: the same rounding), 3 operations more.
