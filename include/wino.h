@@ -145,9 +145,9 @@ extern "C" {
  * 16) goes to the workspace in every call.  AUTO asks for exactly that where it
  * would else run the fused kernel, for the workspace of the split algorithm or of
  * the 1-D stages where it would else run those, and for the split U, the split V
- * and M on deep layers; with less than it asks for it runs the algorithm that
- * wino_plan_r names, or the fused kernel.  An explicitly chosen algorithm always
- * runs on fp32 MFMA. */
+ * and M on deep layers; with less than it asks for, or a workspace that is not
+ * 16-byte aligned, it runs the algorithm that wino_plan_r names, or the fused
+ * kernel.  An explicitly chosen algorithm always runs on fp32 MFMA. */
 
 /* Human-readable text of a status code (static storage, never NULL). */
 const char* wino_status_string(int status);
@@ -199,9 +199,10 @@ int wino_plan_r(int N, int C, int H, int W, int K, int pad, int m, int r, unsign
  *   workspace / workspace_bytes : device scratch of at least
  *       wino_workspace_bytes(N,C,H,W,K,pad,m,flags) bytes (V and M of the staged
  *       algorithm, the tile-blocked V of the split one, the partial outputs of
- *       channel slices); may be NULL/0 when that is 0.  With WINO_ALGO_AUTO the
- *       planner uses the split algorithm or channel slices only if the
- *       workspace given is large enough, else the plain fused kernel (or
+ *       channel slices, the split filters of the kernels on the bf16 matrix
+ *       cores); may be NULL/0 when that is 0.  With WINO_ALGO_AUTO the
+ *       planner uses the split algorithm, channel slices or those kernels only if
+ *       the workspace given is large enough, else the plain fused kernel (or
  *       WINO_ERR_WORKSPACE where the fused kernel's offsets would not fit, see
  *       the size limits above).  Contents on
  *       return are unspecified; calls sharing one workspace must not overlap in

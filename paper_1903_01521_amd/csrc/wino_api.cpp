@@ -198,6 +198,10 @@ size_t stage3_bytes(const Geom& g) {
     return round_up(us_bytes(g), 256) + round_up(v3_bytes(g), 256) + m_elems(g) * sizeof(float);
 }
 
+// These kernels store and load the workspace 16 bytes at a time; one that is not so
+// aligned counts as none for them (the fused kernel they replace needs none at all).
+bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
+
 // The three stages with the GEMMs on the bf16 matrix cores (NCHW or NHWC).
 hipError_t run_g3(const float* x, const float* U, float* y, void* ws, const Geom& g, bool relu, hipStream_t s) {
     char* V = (char*)ws + round_up(us_bytes(g), 256);
@@ -609,10 +613,14 @@ int wino_conv2d_r(const float* x, const float* U, float* y, int N, int C, int H,
             return WINO_ERR_INVALID_ARG;
         return hip_status(launch_staged16(x, U, y, workspace, (float*)((char*)workspace + vb), g, prec, relu, s));
     }
-    if (p.g3 && workspace && workspace_bytes >= p.need3) {
+    if (p.g3 && workspace && aligned16(workspace) && workspace_bytes >= p.need3) {
         if (overlap(workspace, p.need3, x, xb) || overlap(workspace, p.need3, y, yb) || overlap(workspace, p.need3, U, ub))
             return WINO_ERR_INVALID_ARG;
         return hip_status(run_g3(x, U, y, workspace, g, relu, s));
+    }
+    if (p.bf3 && !aligned16(workspace)) {
+        p.bf3 = false;
+        if (!plan_fits(g, p)) return WINO_ERR_WORKSPACE;
     }
     if (p.algo == WINO_ALGO_SPLIT || p.bf3) {
         const size_t need = p.need;
@@ -783,7 +791,7 @@ int wino_conv2d_1d(const float* x, const float* U, float* y, int N, int C, int H
     if (overlap(workspace, need, x, xb) || overlap(workspace, need, y, yb) || overlap(workspace, need, U, ub))
         return WINO_ERR_INVALID_ARG;
     hipStream_t s = (hipStream_t)stream;
-    if (p.bf3) return hip_status(launch_bf3_1d(x, U, y, workspace, g, (flags & WINO_FLAG_RELU) != 0, s));
+    if (p.bf3 && aligned16(workspace)) return hip_status(launch_bf3_1d(x, U, y, workspace, g, (flags & WINO_FLAG_RELU) != 0, s));
     float* V = (float*)workspace;
     float* M = (float*)((char*)workspace + vb);
     st = hip_status(launch_input_transform(x, V, g, s));
@@ -818,7 +826,7 @@ int wino_conv2d_nhwc(const float* x, const float* U, float* y, int N, int C, int
     const size_t ub = wino_filter_bytes(C, K, m);
     if (overlap(x, xb, y, yb) || overlap(U, ub, y, yb)) return WINO_ERR_INVALID_ARG;
     hipStream_t s = (hipStream_t)stream;
-    if (p.g3 && workspace && workspace_bytes >= p.need3) {
+    if (p.g3 && workspace && aligned16(workspace) && workspace_bytes >= p.need3) {
         if (overlap(workspace, p.need3, x, xb) || overlap(workspace, p.need3, y, yb) || overlap(workspace, p.need3, U, ub))
             return WINO_ERR_INVALID_ARG;
         return hip_status(run_g3(x, U, y, workspace, g, (flags & WINO_FLAG_RELU) != 0, s));

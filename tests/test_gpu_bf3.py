@@ -156,6 +156,28 @@ def test_bf3_range(scale):
     assert h.normwise_err(_conv(x, g, m, r), _reference(x, g, r)) <= TOL[m]
 
 
+@pytest.mark.parametrize("shape", [SHAPES[4], SHAPES[6], (13, 205, 12, 11, 476, 2, 5)], ids=["bf3", "bf3_5x5", "gemm3"])
+def test_workspace_not_16_byte_aligned(shape):
+    # counts as none: the fused kernel, which needs none
+    N, C, H, W, K, m, r = shape
+    print(f"bf3 unaligned workspace shape={shape}", flush=True)
+    st, algo, _ = B.wino_plan_r(N, C, H, W, K, r // 2, m, r, 0)
+    assert st == B.WINO_OK and algo == B.WINO_ALGO_FUSED
+    rng = np.random.default_rng(10)
+    x = h.dev(rng.standard_normal((N, C, H, W)))
+    g = h.dev(rng.standard_normal((K, C, r, r)) * np.sqrt(2.0 / (r * r * C)))
+    U = h.empty_bytes(B.wino_filter_bytes_r(C, K, m, r))
+    B.check(B.wino_filter_transform_r(g, U, C, K, m, r))
+    wsb = B.wino_workspace_bytes_r(N, C, H, W, K, r // 2, m, r, 0)
+    assert wsb > 0
+    ws, out = h.empty_bytes(wsb + 16), []
+    for flags, w, n in ((0, ws[1:], wsb), (algo, None, 0), (0, ws[4:], wsb)):
+        y = h.empty_bytes(4 * N * K * H * W)
+        B.check(B.wino_conv2d_r(x, U, y, N, C, H, W, K, r // 2, m, r, flags, w, n))
+        out.append(h.host(y))
+    assert np.array_equal(out[0], out[1]) and not np.array_equal(out[2], out[1])
+
+
 @pytest.mark.parametrize("shape", [SHAPES[4], SHAPES[8]], ids=["fused", "split"])
 def test_bf3_without_its_workspace(shape):
     # a byte less than AUTO asks for: the fused kernel
